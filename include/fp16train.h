@@ -356,13 +356,11 @@ size_t fp16_conv_bn_workspace_bytes(const fp16_conv_desc* conv, const fp16_bn_de
  *   y = fp16_conv_fwd(conv, x, w)              (bit-identical to that call)
  *   mean, rstd of y per channel                 (written to stats[0..2C))
  *   z = the BN apply of fp16_bn_relu on y with those statistics.
- * The epilogue keeps, per 128-row tile of y and channel, a shift K (the
+ * The epilogue keeps, per tile of rows of y and channel, a shift K (the
  * tile's first value) and float32 sums of (y - K) and (y - K)^2 over its
- * rounded values; the tiles are combined in float64.  (Shapes whose
- * convolution kernel does not take the statistics -- the LDS-staged one,
- * used for channel counts that are not a multiple of 32 and for long
- * reductions over large outputs with fewer than 64-multiple channels -- run
- * the convolution and the BN's own statistics pass instead, with the same
+ * rounded values; the tiles are combined in float64.  (Where the convolution
+ * runs on a kernel without that epilogue -- 3x3 stride-1 over 64 channels on
+ * large batches -- the BN's own statistics pass runs instead, with the same
  * results as the two separate calls.)  The statistics may differ from
  * fp16_bn_relu's in the last
  * bits (another summation grouping); z is bit-exact against the declared

@@ -893,12 +893,15 @@ static fp16_status check_conv_bn(const fp16_conv_desc* cd, const fp16_bn_desc* b
   return FP16_OK;
 }
 
-// Tile records ([nb][3][K] float32, 128 rows each) and the statistics'
-// per-slice sums after the convolution's own workspace; when the kernel picked
+// Tile records ([nb][3][K] float32, at least 128 rows each, or 64 for few
+// rows) and the statistics' per-slice sums after the convolution's own workspace; when the kernel picked
 // for the convolution does not take the statistics, the BN's own workspace
 // takes that place instead.
 static size_t conv_bn_band_off(const ConvDims& d) { return conv_ws(d, FP16_PASS_FWD).total; }
-static int conv_bn_nb(const ConvDims& d) { return (int)(((int64_t)d.N * d.P * d.Q + 127) / 128); }
+static int conv_bn_nb(const ConvDims& d) {
+  const int64_t M = (int64_t)d.N * d.P * d.Q;
+  return (int)(M <= kStatSmallRows ? (M + 63) / 64 : (M + 127) / 128);
+}
 
 size_t fp16_conv_bn_workspace_bytes(const fp16_conv_desc* conv, const fp16_bn_desc* bn) {
   ConvDims d;
@@ -991,6 +994,7 @@ static fp16_status conv_bn_impl(const fp16_conv_desc* conv, const fp16_bn_desc* 
   }
   a.stat = part;
   a.stat_nb = igemm_stat_records(a);  // at most conv_bn_nb(d), which sizes the space
+  const int stat_rows = igemm_stat_rows(a);
   TRY(launch_igemm(a, st));
   void* band_ws = reinterpret_cast<char*>(part) +
                   align256((size_t)3 * d.K * a.stat_nb * sizeof(float));
@@ -1000,7 +1004,7 @@ static fp16_status conv_bn_impl(const fp16_conv_desc* conv, const fp16_bn_desc* 
     // the statistics, then a second pass of the convolution that recomputes
     // y bit for bit from x and writes z = the BN apply of it (with the
     // shortcut and the kept ReLU mask) instead of reading y back
-    TRY(launch_bn_band_stats(b, part, a.stat_nb, band_ws, stats, st));
+    TRY(launch_bn_band_stats(b, part, a.stat_nb, stat_rows, band_ws, stats, st));
     z2.out = reinterpret_cast<h16*>(z);
     z2.bn_stats = stats;
     z2.bn_gamma = gp;
@@ -1012,7 +1016,7 @@ static fp16_status conv_bn_impl(const fp16_conv_desc* conv, const fp16_bn_desc* 
     z2.bn_swap = b.swap;
     return hip_status(launch_igemm(z2, st));
   }
-  return hip_status(launch_bn_fwd_bands(b, part, a.stat_nb, band_ws,
+  return hip_status(launch_bn_fwd_bands(b, part, a.stat_nb, stat_rows, band_ws,
                                         reinterpret_cast<const h16*>(y),
                                         reinterpret_cast<const h16*>(gamma),
                                         reinterpret_cast<const h16*>(beta),

@@ -347,8 +347,8 @@ __global__ __launch_bounds__(64 * kFinW) void bn_fwd_finalize_bm(const h16* __re
 }
 
 // Statistics from the records a convolution's epilogue wrote ([nb][3][C]:
-// record b covers the 128-row tiles b, b + nb, b + 2nb, ... (one tile each
-// where nb is the tile count) and holds per channel c a shift K_b (one of its
+// record b covers the tiles b, b + nb, b + 2nb, ... of `rows` rows each (one
+// tile each where nb is the tile count) and holds per channel c a shift K_b (one of its
 // values) and the sums of (y - K_b) and (y - K_b)^2 over its n_b rows).
 // About K_0:
 //   S1 = sum_b s1_b + n_b d_b,  S2 = sum_b s2_b + 2 d_b s1_b + n_b d_b^2,
@@ -367,13 +367,13 @@ __global__ __launch_bounds__(64 * kFinW) void bn_fwd_finalize_bm(const h16* __re
 constexpr int kBandOne = 2048;
 constexpr int kBandRps = 32;  // records per slice: 8 per wave
 
-// Rows of record j of nb over M rows: 128 per tile it covers, less the
+// Rows of record j of nb over M rows: `rows` per tile it covers, less the
 // last tile's missing rows where that tile is its.
-__device__ __forceinline__ int64_t band_rows(int64_t M, int nb, int j) {
-  const int64_t nt = (M + 127) / 128;
+__device__ __forceinline__ int64_t band_rows(int64_t M, int nb, int rows, int j) {
+  const int64_t nt = (M + rows - 1) / rows;
   if (j >= nt) return 0;
-  int64_t r = 128 * ((nt - 1 - j) / nb + 1);
-  if (j == (nt - 1) % nb) r -= 128 * nt - M;
+  int64_t r = rows * ((nt - 1 - j) / nb + 1);
+  if (j == (nt - 1) % nb) r -= rows * nt - M;
   return r;
 }
 
@@ -398,7 +398,7 @@ __device__ __forceinline__ void band_stats(double a, double b, double K0, Geo g,
 }
 
 __global__ __launch_bounds__(256) void bn_band_finalize(const float* __restrict__ part, int nb,
-                                                        Geo g, float eps, float* stats) {
+                                                        int rows, Geo g, float eps, float* stats) {
   __shared__ double red[2][4];
   const int c = blockIdx.x;
   const int t = threadIdx.x;
@@ -419,7 +419,7 @@ __global__ __launch_bounds__(256) void bn_band_finalize(const float* __restrict_
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int j = j0 + 256 * u;
-      band_term_if(j < nb, band_rows(g.M, nb, j), k[u], K0, s1[u], s2[u], a, b);
+      band_term_if(j < nb, band_rows(g.M, nb, rows, j), k[u], K0, s1[u], s2[u], a, b);
     }
   }
 #pragma unroll
@@ -438,7 +438,7 @@ __global__ __launch_bounds__(256) void bn_band_finalize(const float* __restrict_
 }
 
 __global__ __launch_bounds__(256) void bn_band_slices(const float* __restrict__ part, int nb,
-                                                      Geo g, double* __restrict__ sl, int ns) {
+                                                      int rows, Geo g, double* __restrict__ sl, int ns) {
   __shared__ double red[2][4][64];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   const int c = blockIdx.x * 64 + lane;
@@ -460,7 +460,7 @@ __global__ __launch_bounds__(256) void bn_band_slices(const float* __restrict__ 
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int j = s * kBandRps + w + 4 * u;
-      band_term_if(j < nb, band_rows(g.M, nb, j), k[u], K0, s1[u], s2[u], a, b);
+      band_term_if(j < nb, band_rows(g.M, nb, rows, j), k[u], K0, s1[u], s2[u], a, b);
     }
   }
   red[0][w][lane] = a;
@@ -1086,28 +1086,29 @@ size_t bn_band_ws_bytes(int C, int nb) {
   return align256((size_t)2 * C * ns * sizeof(double));
 }
 
-hipError_t launch_bn_band_stats(const BnArgs& a, const float* part, int nb, void* band_ws,
+hipError_t launch_bn_band_stats(const BnArgs& a, const float* part, int nb, int rows, void* band_ws,
                                 float* stats, hipStream_t st) {
   const Geo g = make_geo(a);
   if (nb <= kBandOne) {
-    hipLaunchKernelGGL(bn_band_finalize, dim3(a.C), dim3(256), 0, st, part, nb, g, a.eps, stats);
+    hipLaunchKernelGGL(bn_band_finalize, dim3(a.C), dim3(256), 0, st, part, nb, rows, g, a.eps,
+                       stats);
   } else {
     const int ns = (nb + kBandRps - 1) / kBandRps;
     double* sl = reinterpret_cast<double*>(band_ws);
-    hipLaunchKernelGGL(bn_band_slices, dim3((a.C + 63) / 64, ns), dim3(256), 0, st, part, nb, g,
-                       sl, ns);
+    hipLaunchKernelGGL(bn_band_slices, dim3((a.C + 63) / 64, ns), dim3(256), 0, st, part, nb, rows,
+                       g, sl, ns);
     hipLaunchKernelGGL(bn_band_combine, dim3(a.C), dim3(64), 0, st, part, sl, ns, g, a.eps,
                        stats);
   }
   return hipGetLastError();
 }
 
-hipError_t launch_bn_fwd_bands(const BnArgs& a, const float* part, int nb, void* band_ws,
+hipError_t launch_bn_fwd_bands(const BnArgs& a, const float* part, int nb, int rows, void* band_ws,
                                const h16* x, const h16* gamma, const h16* beta, const h16* res,
                                h16* y, float* stats, uint8_t* mout, hipStream_t st) {
   const Plan p = make_plan(a);
   const Geo g = make_geo(a);
-  const hipError_t es = launch_bn_band_stats(a, part, nb, band_ws, stats, st);
+  const hipError_t es = launch_bn_band_stats(a, part, nb, rows, band_ws, stats, st);
   if (es != hipSuccess) return es;
   if (p.vec) {
     const hipError_t e =

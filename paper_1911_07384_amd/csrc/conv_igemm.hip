@@ -14,24 +14,25 @@
 // image (or a row past the end) gets an out-of-range offset and reads zeros,
 // with no branch.
 //
-// Three kernels, all v_mfma_f32_32x32x16_f16 with float32 accumulators and
-// the same k order (so they give identical bits):
-//   igemm_kernel  -- 4 waves in a 2x2 or 4x1 grid; A and B tiles staged in
-//                    LDS through registers, k-step 64, double buffered.
+// The kernels, all v_mfma_f32_32x32x16_f16 with float32 accumulators:
+//   igemm8_kernel -- eight waves and a tile of 64 to 256 rows chosen per
+//                    problem, both operands DMA'd straight from global memory
+//                    into a ring of three LDS stages, the DMAs spread between
+//                    the MFMAs: everything the others do not take, any
+//                    channel count and filter.
 //   igemm4_kernel -- 4 waves split M only, so no A element is shared: each
 //                    lane loads its own MFMA operand rows from global memory
 //                    into registers three k-steps ahead, and only the filter
 //                    tile goes through LDS, by DMA (buffer_load ... lds) into
 //                    four stage buffers with XOR-swizzled rows.  Needs
-//                    Ci % 32 == 0.  Less LDS traffic per MFMA; wins on short
-//                    reductions and small M.
-//   igemm7_kernel -- both operands DMA'd straight from global memory into a
-//                    ring of LDS stages, k-step 64 so that each operand row
-//                    of a stage is one whole 128-byte line, per-row tap masks
-//                    precomputed so a DMA costs a few ALU operations, and the
-//                    MFMA operands read one k sub-step ahead.  Needs
-//                    Ci % 64 == 0; wins on the long reductions (every 3x3
-//                    layer).
+//                    Ci % 32 == 0.  Short reductions over many rows.
+//   igemm7_kernel -- 128 x 128 tiles at two workgroups per CU, both operands
+//                    DMA'd into two LDS stages, k-step 64 so that each operand
+//                    row of a stage is one whole 128-byte line, per-row tap
+//                    masks precomputed so a DMA costs a few ALU operations,
+//                    and the MFMA operands read one k sub-step ahead.  Needs
+//                    Ci % 64 == 0; the mid-length phases of strided data
+//                    gradients.
 //   pw_kernel     -- 1x1 filters with 64 or 128 input channels (or 256
 //                    without an addend) and a dense output of 128+ channels
 //                    (bound by the output's bytes): the filter tile stays in
@@ -43,15 +44,17 @@
 //                    epilogue can take the following BN's statistics, or
 //                    (a second pass) apply that BN to the recomputed output.
 //
-// Epilogue (the first three): each wave stages a 32-row band of its float32
-// tile in LDS and writes whole output rows with 16-byte stores.  Every value is rounded
-// once to binary16 (RNE), optionally after adding a binary16 addend in
-// float32.  igemm4_kernel and igemm7_kernel can also take the statistics of a
-// BN that follows the convolution, without a second pass over the output:
-// per 128-row tile and channel, shifted sums of the rounded values
+// Epilogue: tiles go through LDS (or lane-half swaps) so that whole output
+// rows are written with 16-byte stores.  Every value is rounded once to
+// binary16 (RNE), optionally after adding a binary16 addend in float32.
+// igemm8_kernel, igemm4_kernel and pw_kernel can also take the statistics of a
+// BN that follows the convolution, without a second pass over the output: per
+// tile of rows and channel, shifted sums of the rounded values
 // (IgemmArgs::stat).
 
 #include "kernels.hpp"
+
+#include <type_traits>
 
 
 namespace fp16k {
@@ -116,220 +119,6 @@ __device__ __forceinline__ void xcd_tile(int gn, int& z, int& mt, int& nt) {
   nt = g * gn + w % gw;
   mt = w / gw;
 }
-
-template <int BM, int BN, int WM, int WN, int BK>
-struct Cfg {
-  static constexpr int LDK = BK + 8;
-  static constexpr int KC = BK / 8;           // 16-byte chunks per tile row
-  static constexpr int RSTEP = 256 / KC;      // rows covered per load pass
-  static constexpr int WTM = BM / WM, WTN = BN / WN;
-  static constexpr int TM = WTM / 32, TN = WTN / 32;
-  static constexpr int A_IT = BM / RSTEP;
-  static constexpr int B_IT = BN / RSTEP;
-  static constexpr int SP = WTN + 4;
-  static constexpr int MAIN_BYTES = 2 * (BM + BN) * LDK * 2;
-  static constexpr int STAGE_BYTES = 4 * 32 * SP * 4;
-  static constexpr int LDS_BYTES = MAIN_BYTES > STAGE_BYTES ? MAIN_BYTES : STAGE_BYTES;
-};
-
-template <int BM, int BN, int WM, int WN, int BK>
-__global__ __launch_bounds__(256) void igemm_kernel(const IgemmArgs a) {
-  using K = Cfg<BM, BN, WM, WN, BK>;
-  constexpr int LDK = K::LDK, KC = K::KC, RSTEP = K::RSTEP;
-  constexpr int WTM = K::WTM, WTN = K::WTN, TM = K::TM, TN = K::TN;
-  constexpr int A_IT = K::A_IT, B_IT = K::B_IT;
-  static_assert(WM * WN == 4, "four waves");
-  static_assert(TM >= 1 && TN >= 1 && A_IT >= 1 && B_IT >= 1, "tile shape");
-
-  __shared__ __attribute__((aligned(16))) char smem[K::LDS_BYTES];
-  h16* As = reinterpret_cast<h16*>(smem);
-  h16* Bs = As + 2 * BM * LDK;
-
-  int tz, tm_, tn_;
-  xcd_tile(a.gn, tz, tm_, tn_);
-  const IgemmPhase ph = a.ph[tz];
-  const int HoWo = ph.Ho * ph.Wo;
-  const int M = a.N * HoWo;
-  const int m0 = tm_ * BM;
-  if (m0 >= M) return;
-  const int n0 = tn_ * BN;
-  const int Ci = a.Ci;
-  const int Kg = ph.Rt * ph.St * Ci;
-  const int tid = threadIdx.x;
-  const int kc = tid % KC;
-  const int rbase = tid / KC;
-
-  int64_t a_base[A_IT];
-  int a_ih0[A_IT], a_iw0[A_IT];
-#pragma unroll
-  for (int it = 0; it < A_IT; ++it) {
-    const int m = m0 + rbase + it * RSTEP;
-    if (m < M) {
-      const int img = m / HoWo;
-      const int rem = m - img * HoWo;
-      const int i = rem / ph.Wo;
-      const int j = rem - i * ph.Wo;
-      a_base[it] = (int64_t)img * a.Hi * a.Wi * Ci;
-      a_ih0[it] = i * a.stride_h - ph.pad_h;
-      a_iw0[it] = j * a.stride_w - ph.pad_w;
-    } else {
-      a_base[it] = 0;
-      a_ih0[it] = -(1 << 28);
-      a_iw0[it] = 0;
-    }
-  }
-
-  // range-checked buffer loads: an offset past the end reads zeros, no branch
-  const uint32_t act_bytes = (uint32_t)((int64_t)a.N * a.Hi * a.Wi * Ci * 2);
-  const __amdgpu_buffer_rsrc_t rs_a = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<h16*>(a.act), (short)0, (int)act_bytes, 0x00020000);
-  const uint32_t filt_bytes = (uint32_t)((int64_t)a.Co * ph.ldb * 2);
-  const __amdgpu_buffer_rsrc_t rs_b = __builtin_amdgcn_make_buffer_rsrc(
-      const_cast<h16*>(ph.filt), (short)0, (int)filt_bytes, 0x00020000);
-  constexpr uint32_t OOB = 0x80000000u;
-  uint32_t a_off[A_IT];
-#pragma unroll
-  for (int it = 0; it < A_IT; ++it) a_off[it] = (uint32_t)(a_base[it] * 2);
-  auto load_tile = [&](int k0, V8 (&ra)[A_IT], V8 (&rb)[B_IT]) {
-    const int kk = k0 + kc * 8;
-    const bool kval = kk < Kg;
-    const int tap = kval ? kk / Ci : 0;
-    const int c = kk - tap * Ci;
-    const int r = tap / ph.St;
-    const int s = tap - r * ph.St;
-#pragma unroll
-    for (int it = 0; it < A_IT; ++it) {
-      const int ih = a_ih0[it] + r;
-      const int iw = a_iw0[it] + s;
-      const bool v = kval && (unsigned)ih < (unsigned)a.Hi && (unsigned)iw < (unsigned)a.Wi;
-      const uint32_t off = v ? a_off[it] + (uint32_t)((ih * a.Wi + iw) * Ci + c) * 2u : OOB;
-      ra[it].u = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs_a, off, 0, 0));
-    }
-#pragma unroll
-    for (int it = 0; it < B_IT; ++it) {
-      const int n = n0 + rbase + it * RSTEP;
-      const uint32_t off = (kval && n < a.Co) ? (uint32_t)(n * ph.ldb + kk) * 2u : OOB;
-      rb[it].u = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs_b, off, 0, 0));
-    }
-  };
-  auto store_tile = [&](int buf, const V8 (&ra)[A_IT], const V8 (&rb)[B_IT]) {
-    h16* as = As + buf * BM * LDK;
-    h16* bs = Bs + buf * BN * LDK;
-#pragma unroll
-    for (int it = 0; it < A_IT; ++it) store16(&as[(rbase + it * RSTEP) * LDK + kc * 8], ra[it]);
-#pragma unroll
-    for (int it = 0; it < B_IT; ++it) store16(&bs[(rbase + it * RSTEP) * LDK + kc * 8], rb[it]);
-  };
-
-  const int wave = tid >> 6, lane = tid & 63;
-  const int wm = wave / WN, wn = wave % WN;
-  const int lrow = lane & 31, lk = (lane >> 5) * 8;
-
-  floatx16 acc[TM][TN];
-#pragma unroll
-  for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-    for (int tn = 0; tn < TN; ++tn)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[tm][tn][e] = 0.0f;
-
-  auto compute = [&](int buf) {
-    const h16* as = As + buf * BM * LDK;
-    const h16* bs = Bs + buf * BN * LDK;
-#pragma unroll
-    for (int ks = 0; ks < BK / 16; ++ks) {
-      half8 af[TM], bf[TN];
-#pragma unroll
-      for (int tm = 0; tm < TM; ++tm)
-        af[tm] = *reinterpret_cast<const half8*>(&as[(wm * WTM + tm * 32 + lrow) * LDK + ks * 16 + lk]);
-#pragma unroll
-      for (int tn = 0; tn < TN; ++tn)
-        bf[tn] = *reinterpret_cast<const half8*>(&bs[(wn * WTN + tn * 32 + lrow) * LDK + ks * 16 + lk]);
-#pragma unroll
-      for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-        for (int tn = 0; tn < TN; ++tn) {
-          acc[tm][tn] = mfma32x32x16(af[tm], bf[tn], acc[tm][tn]);
-        }
-    }
-  };
-
-  const int KT = (Kg + BK - 1) / BK;
-  V8 ra0[A_IT], rb0[B_IT];
-  if (KT > 0) {
-    load_tile(0, ra0, rb0);
-    store_tile(0, ra0, rb0);
-  }
-  __syncthreads();
-  for (int kt = 0; kt < KT; ++kt) {
-    if (kt + 1 < KT) load_tile((kt + 1) * BK, ra0, rb0);
-    compute(kt & 1);
-    if (kt + 1 < KT) store_tile((kt + 1) & 1, ra0, rb0);
-    __syncthreads();
-  }
-
-  float* stg = reinterpret_cast<float*>(smem) + wave * 32 * K::SP;
-  constexpr int CPR = WTN / 8;
-  constexpr int RPP = 64 / CPR;
-  const int cc = lane % CPR;
-  const int rr = lane / CPR;
-  const int n = n0 + wn * WTN + cc * 8;
-  const bool vec_ok = (a.ldo % 8) == 0 && n + 8 <= a.Co;
-#pragma unroll
-  for (int tm = 0; tm < TM; ++tm) {
-#pragma unroll
-    for (int tn = 0; tn < TN; ++tn)
-#pragma unroll
-      for (int e = 0; e < 16; ++e)
-        stg[(8 * (e >> 2) + 4 * (lane >> 5) + (e & 3)) * K::SP + tn * 32 + lrow] = acc[tm][tn][e];
-    __syncthreads();
-#pragma unroll
-    for (int pass = 0; pass < 32 / RPP; ++pass) {
-      const int r = pass * RPP + rr;
-      const int m = m0 + wm * WTM + tm * 32 + r;
-      if (m < M && n < a.Co) {
-        const int img = m / HoWo;
-        const int rem = m - img * HoWo;
-        const int i = rem / ph.Wo;
-        const int j = rem - i * ph.Wo;
-        const int oh = i * a.os_h + ph.oph;
-        const int ow = j * a.os_w + ph.opw;
-        const int64_t off = ((int64_t)(img * a.OH + oh) * a.OW + ow) * a.ldo + n;
-        const float* src = stg + r * K::SP + cc * 8;
-        float v[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = src[e];
-        if (vec_ok) {
-          if (a.addend) {
-            const int64_t ar = addend_row(a, img, oh, ow);
-            const V8 ad = ar >= 0 ? addend8(a, ar + n) : zero8();
-#pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] += to_f32(ad.h[e]);
-          }
-          V8 o;
-#pragma unroll
-          for (int e = 0; e < 8; ++e) o.h[e] = to_h16(v[e]);
-          store16(a.out + off, o);
-        } else {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            if (n + e < a.Co) {
-              float x = v[e];
-              if (a.addend) {
-                const int64_t ar = addend_row(a, img, oh, ow);
-                x += ar >= 0 ? addend1(a, ar + n + e) : 0.0f;
-              }
-              a.out[off + e] = to_h16(x);
-            }
-          }
-        }
-      }
-    }
-    __syncthreads();
-  }
-}
-
-
 
 // ---- A from global into VGPRs, B (filter) through LDS by DMA ---------------
 // Four waves split M only, so no A element is shared between waves: each
@@ -1225,21 +1014,15 @@ struct Cfg7 {
   static constexpr int IA = BM / 32, IB = BN / 32;  // DMA instructions per wave per stage
   static constexpr int Q = IA + IB;
   static constexpr int STAGE = (BM + BN) * 128;     // bytes
-  static constexpr int SP = 32 * TN + 4;            // epilogue staging pitch (floats)
-  static constexpr int EPI = 4 * 32 * SP * 4;
-  // BN statistics of the epilogue: [WN][4 bands][3][32*TN] floats + 4 row
-  // counts, after the staging area
-  static constexpr int STAT = WN * 4 * 3 * 32 * TN * 4 + 16;
-  static constexpr int LDS = S * STAGE > EPI + STAT ? S * STAGE : EPI + STAT;
+  static constexpr int LDS = S * STAGE;
 };
 
-// TRANS (without statistics): the MFMA operands are swapped so that the
-// accumulators hold the transposed tile, and the epilogue writes straight from
-// registers after lane-half swaps, as pw_kernel does (no LDS staging).
-template <int TM, int TN, int WM, int WN, int S, bool STATS, bool TRANS = !STATS>
+// The MFMA operands are swapped so that the accumulators hold the transposed
+// tile, and the epilogue writes straight from registers after lane-half swaps,
+// as pw_kernel does (no LDS staging).
+template <int TM, int TN, int WM, int WN, int S>
 __global__ __launch_bounds__(256) void igemm7_kernel(const IgemmArgs a) {
   using K = Cfg7<TM, TN, WM, WN, S>;
-  static_assert(!(STATS && TRANS), "statistics are taken from the staged tile");
   constexpr int BM = K::BM, BN = K::BN, IA = K::IA, IB = K::IB;
   static_assert(WM * WN == 4 && IA >= 1 && IB >= 1 && S >= 2, "tile shape");
   static_assert(K::Q * (S - 1) < 64, "vmcnt range");
@@ -1360,8 +1143,7 @@ __global__ __launch_bounds__(256) void igemm7_kernel(const IgemmArgs a) {
     for (int tm = 0; tm < TM; ++tm)
 #pragma unroll
       for (int tn = 0; tn < TN; ++tn)
-        acc[tm][tn] = TRANS ? mfma32x32x16(fb[tn], fa[tm], acc[tm][tn])
-                            : mfma32x32x16(fa[tm], fb[tn], acc[tm][tn]);
+        acc[tm][tn] = mfma32x32x16(fb[tn], fa[tm], acc[tm][tn]);
   };
 
   const int KT = (Kg + 63) / 64;
@@ -1393,154 +1175,78 @@ __global__ __launch_bounds__(256) void igemm7_kernel(const IgemmArgs a) {
     mma(af[1], bf[1]);
   }
   __builtin_amdgcn_s_waitcnt(0);
-  if (TRANS) {
-    // lane: output pixel m (lane % 32 of each 32-row tile) and, after the
-    // swaps, channels 16h + 8*(lane/32) + 0..7 of each 32-channel tile
-    V8 adv[TM][TN][2];
-    uint32_t amb[TM][TN][2];
+  // lane: output pixel m (lane % 32 of each 32-row tile) and, after the
+  // swaps, channels 16h + 8*(lane/32) + 0..7 of each 32-channel tile
+  V8 adv[TM][TN][2];
+  uint32_t amb[TM][TN][2];
 #pragma unroll
-    for (int tm = 0; tm < TM; ++tm) {
-      const int m = m0 + wm * 32 * TM + tm * 32 + lrow;
-      int64_t base = 0, abase = -1;  // abase: the addend's row, -1 for +0
-      if (m < M) {
-        const int img = m / HoWo;
-        const int rem = m - img * HoWo;
-        const int i = rem / ph.Wo;
-        const int j = rem - i * ph.Wo;
-        const int oh = i * a.os_h + ph.oph, ow = j * a.os_w + ph.opw;
-        base = ((int64_t)(img * a.OH + oh) * a.OW + ow) * a.ldo;
-        if (a.addend) abase = addend_row(a, img, oh, ow);
-      }
-      if (a.addend && (a.ldo % 8) == 0) {
-        // the addend first, so its loads overlap the swaps and conversions
+  for (int tm = 0; tm < TM; ++tm) {
+    const int m = m0 + wm * 32 * TM + tm * 32 + lrow;
+    int64_t base = 0, abase = -1;  // abase: the addend's row, -1 for +0
+    if (m < M) {
+      const int img = m / HoWo;
+      const int rem = m - img * HoWo;
+      const int i = rem / ph.Wo;
+      const int j = rem - i * ph.Wo;
+      const int oh = i * a.os_h + ph.oph, ow = j * a.os_w + ph.opw;
+      base = ((int64_t)(img * a.OH + oh) * a.OW + ow) * a.ldo;
+      if (a.addend) abase = addend_row(a, img, oh, ow);
+    }
+    if (a.addend && (a.ldo % 8) == 0) {
+      // the addend first, so its loads overlap the swaps and conversions
+#pragma unroll
+      for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int n = n0 + wn * 32 * TN + tn * 32 + h * 16 + lhi * 8;
+          if (abase >= 0 && n + 8 <= a.Co) adv[tm][tn][h] = load16(a.addend + abase + n);
+        }
+      if (a.amask) {
 #pragma unroll
         for (int tn = 0; tn < TN; ++tn)
 #pragma unroll
           for (int h = 0; h < 2; ++h) {
             const int n = n0 + wn * 32 * TN + tn * 32 + h * 16 + lhi * 8;
-            if (abase >= 0 && n + 8 <= a.Co) adv[tm][tn][h] = load16(a.addend + abase + n);
+            if (abase >= 0 && n + 8 <= a.Co) amb[tm][tn][h] = a.amask[(abase + n) >> 3];
           }
-        if (a.amask) {
-#pragma unroll
-          for (int tn = 0; tn < TN; ++tn)
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-              const int n = n0 + wn * 32 * TN + tn * 32 + h * 16 + lhi * 8;
-              if (abase >= 0 && n + 8 <= a.Co) amb[tm][tn][h] = a.amask[(abase + n) >> 3];
-            }
-        }
-      }
-#pragma unroll
-      for (int tn = 0; tn < TN; ++tn) {
-        float v[16];
-#pragma unroll
-        for (int e = 0; e < 16; ++e) v[e] = acc[tm][tn][e];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          lane_half_swap(v[q], v[4 + q]);
-          lane_half_swap(v[8 + q], v[12 + q]);
-        }
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-          const int n = n0 + wn * 32 * TN + tn * 32 + h * 16 + lhi * 8;
-          if (m >= M || n >= a.Co) continue;
-          const int64_t off = base + n;
-          if ((a.ldo % 8) == 0 && n + 8 <= a.Co) {
-            float w[8];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) w[e] = v[h * 8 + e];
-            if (a.addend) {
-              V8 ad = a.amask ? masked8(adv[tm][tn][h], amb[tm][tn][h]) : adv[tm][tn][h];
-              if (abase < 0) ad = zero8();
-#pragma unroll
-              for (int e = 0; e < 8; ++e) w[e] += to_f32(ad.h[e]);
-            }
-            V8 o;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) o.h[e] = to_h16(w[e]);
-            store16(a.out + off, o);
-          } else {
-#pragma unroll
-            for (int e = 0; e < 8; ++e) {
-              if (n + e < a.Co) {
-                float x = v[h * 8 + e];
-                if (a.addend) {
-                  x += abase >= 0 ? addend1(a, abase + n + e) : 0.0f;
-                }
-                a.out[off + e] = to_h16(x);
-              }
-            }
-          }
-        }
       }
     }
-    return;
-  }
-  __syncthreads();
-
-  float* stg = reinterpret_cast<float*>(lds) + wave * 32 * K::SP;
-  constexpr int CPR = 32 * TN / 8;  // lanes per row
-  constexpr int RPP = 64 / CPR;     // rows per pass
-  const int cc = lane % CPR;
-  const int rr = lane / CPR;
-  const int n = n0 + wn * 32 * TN + cc * 8;
-  const bool vec_ok = (a.ldo % 8) == 0 && n + 8 <= a.Co;
-  // BN statistics of the rounded output (BM == 128: one record per tile):
-  // per 32-row band and channel the band's first value K and the sums of
-  // (y - K), (y - K)^2, taken column by column from the staged band (one lane
-  // per column, rows in order); the four bands are combined in row order below
-  // (kept inside the one LDS array: a second __shared__ object makes the
-  // compiler wait for every LDS DMA in flight before each LDS read)
-  constexpr int NB = 4, CW = 32 * TN;
-  constexpr int RH = 32 * CW / 64;  // rows per lane
-  static_assert(!STATS || BM == 128, "statistics records cover 128 rows");
-  float (*bst)[NB][3][CW] = reinterpret_cast<float (*)[NB][3][CW]>(lds + K::EPI);
-  int* bcnt = reinterpret_cast<int*>(lds + K::EPI + K::STAT - 16);
 #pragma unroll
-  for (int tm = 0; tm < TM; ++tm) {
+    for (int tn = 0; tn < TN; ++tn) {
+      float v[16];
 #pragma unroll
-    for (int tn = 0; tn < TN; ++tn)
+      for (int e = 0; e < 16; ++e) v[e] = acc[tm][tn][e];
 #pragma unroll
-      for (int e = 0; e < 16; ++e)
-        stg[(8 * (e >> 2) + 4 * lhi + (e & 3)) * K::SP + tn * 32 + lrow] = acc[tm][tn][e];
-    __syncthreads();
-    const int band = wm * TM + tm;
-    const int band_m0 = m0 + band * 32;
+      for (int q = 0; q < 4; ++q) {
+        lane_half_swap(v[q], v[4 + q]);
+        lane_half_swap(v[8 + q], v[12 + q]);
+      }
 #pragma unroll
-    for (int pass = 0; pass < 32 / RPP; ++pass) {
-      const int r = pass * RPP + rr;
-      const int m = band_m0 + r;
-      if (m < M && n < a.Co) {
-        const int img = m / HoWo;
-        const int rem = m - img * HoWo;
-        const int i = rem / ph.Wo;
-        const int j = rem - i * ph.Wo;
-        const int oh = i * a.os_h + ph.oph;
-        const int ow = j * a.os_w + ph.opw;
-        const int64_t off = ((int64_t)(img * a.OH + oh) * a.OW + ow) * a.ldo + n;
-        const float* src = stg + r * K::SP + cc * 8;
-        float v[8];
+      for (int h = 0; h < 2; ++h) {
+        const int n = n0 + wn * 32 * TN + tn * 32 + h * 16 + lhi * 8;
+        if (m >= M || n >= a.Co) continue;
+        const int64_t off = base + n;
+        if ((a.ldo % 8) == 0 && n + 8 <= a.Co) {
+          float w[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = src[e];
-        if (vec_ok) {
+          for (int e = 0; e < 8; ++e) w[e] = v[h * 8 + e];
           if (a.addend) {
-            const int64_t ar = addend_row(a, img, oh, ow);
-            const V8 ad = ar >= 0 ? addend8(a, ar + n) : zero8();
+            V8 ad = a.amask ? masked8(adv[tm][tn][h], amb[tm][tn][h]) : adv[tm][tn][h];
+            if (abase < 0) ad = zero8();
 #pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] += to_f32(ad.h[e]);
+            for (int e = 0; e < 8; ++e) w[e] += to_f32(ad.h[e]);
           }
           V8 o;
 #pragma unroll
-          for (int e = 0; e < 8; ++e) o.h[e] = to_h16(v[e]);
+          for (int e = 0; e < 8; ++e) o.h[e] = to_h16(w[e]);
           store16(a.out + off, o);
         } else {
 #pragma unroll
           for (int e = 0; e < 8; ++e) {
             if (n + e < a.Co) {
-              float x = v[e];
+              float x = v[h * 8 + e];
               if (a.addend) {
-                const int64_t ar = addend_row(a, img, oh, ow);
-                x += ar >= 0 ? addend1(a, ar + n + e) : 0.0f;
+                x += abase >= 0 ? addend1(a, abase + n + e) : 0.0f;
               }
               a.out[off + e] = to_h16(x);
             }
@@ -1548,52 +1254,446 @@ __global__ __launch_bounds__(256) void igemm7_kernel(const IgemmArgs a) {
         }
       }
     }
-    if (STATS) {
-      const int rows = M - band_m0 <= 0 ? 0 : (M - band_m0 < 32 ? M - band_m0 : 32);
-      const int c = lane % CW, h = lane / CW;
-      const float Kc = to_f32(to_h16(stg[c]));  // the band's first row, as stored
-      float s1 = 0.0f, s2 = 0.0f;
+  }
+}
+
+// ---- wide tiles: eight waves, one workgroup per CU ---------------------------------
+// igemm7_kernel's 128 x 128 tiles come in counts that fit the 256 CUs badly, and
+// its loads for the next stage are issued all at once after a barrier, where
+// they fill the load path and hold back the MFMAs behind them in every wave.
+// Here a workgroup of eight waves owns BM rows x BN = 32 * WN channels:
+//  - BM is chosen per problem (wide_choice) so that the tiles fill the CUs in
+//    whole rounds.  WN = 4: wave (wm, wn) computes TA (wm = 0) or TB (wm = 1)
+//    32-row tiles of channels 32*wn .. + 31, BM = 32 * (TA + TB); waves w and
+//    w + 4 share a SIMD, so every SIMD holds TA + TB tiles however they are
+//    split.  WN = 2: four row groups of TA tiles, BM = 128 * TA;
+//  - three LDS stages of 64 reduction elements in a ring, rows of whole
+//    128-byte lines as in igemm7_kernel; the stage two ahead is loaded a few
+//    DMAs per sub-step between the MFMAs.  (Measured at batch 128, 14x14 256
+//    -> 256 3x3: 41.0 us on 128 x 128 tiles, 35.2 with BM = 224 and the DMAs
+//    in one burst, 33.8 with them spread; 28x28 128 -> 128: 46.9, 38.7, 37.3;
+//    two groups of four waves splitting each k-step, with 64-column wave tiles
+//    and a third less LDS traffic, 36.4 and 46.9);
+//  - reduction order: 64-channel chunks outside, taps inside, so that a
+//    workgroup's re-reads of its rows for the next tap hit its L1 and the
+//    XCD's L2 (28x28: 43.1 -> 38.7 us against taps outside; 14x14 the same).
+//    Where Ci is not a multiple of 64 (CGEN), the taps are outside and every
+//    lane's 8-channel chunk has a tap of its own.
+// Epilogue: the MFMA operands are swapped (a lane holds one output pixel and,
+// after lane-half swaps, 8 consecutive channels); the rounded 16-byte chunks
+// (or, with an addend, the float32 sums) go through LDS, chunks XOR-swizzled
+// by row, and come back so that BN/8 consecutive lanes store one row's BN
+// channels.  BN statistics are taken there: each thread sums (y - K) and its
+// square for its 8 channels over the tile's rows (K: the tile's first row),
+// the lanes and waves of one chunk combined in a fixed order into one record
+// per BM rows.
+template <int WN, int TA, int TB>
+struct Cfg8 {
+  static constexpr int S = 3;
+  static constexpr int BM = WN == 4 ? 32 * (TA + TB) : 128 * TA, BN = 32 * WN;
+  static constexpr int STAGE = (BM + BN) * 128;  // bytes
+  static constexpr int EPI = BM * BN * 4;        // the float32 tile
+  static constexpr int CPR = BN / 8;             // 16-byte chunks of a row
+  static constexpr int RPP = 512 / CPR;          // rows per pass of the epilogue
+  static constexpr int RED = 8 * 2 * BN * 4;     // statistics: [8 waves][2][BN]
+  static constexpr int LDS = S * STAGE > EPI + RED ? S * STAGE : EPI + RED;
+  static_assert(WN == 4 || (WN == 2 && TA == TB), "wave grid");
+  static_assert(LDS <= 160 * 1024, "LDS");
+};
+
+template <int WN, int TA, int TB, bool STATS, bool ADD, bool CGEN>
+__global__ __launch_bounds__(512, 2) void igemm8_kernel(const IgemmArgs a) {
+  using K = Cfg8<WN, TA, TB>;
+  static_assert(!(STATS && ADD), "statistics are taken without an addend");
+  constexpr int BM = K::BM, BN = K::BN, S = K::S, CPR = K::CPR, RPP = K::RPP;
+  __shared__ __attribute__((aligned(1024))) char lds[K::LDS];
+
+  int tz, tm_, tn_;
+  xcd_tile(a.gn, tz, tm_, tn_);
+  const IgemmPhase ph = a.ph[tz];
+  const int HoWo = ph.Ho * ph.Wo;
+  const int M = a.N * HoWo;
+  const int m0 = tm_ * BM;
+  if (m0 >= M) return;
+  const int n0 = tn_ * BN;
+  const int Ci = a.Ci;
+  const int taps = ph.Rt * ph.St;
+  const int Kg = taps * Ci;
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int lrow = lane & 31, lhi = lane >> 5;
+  const int act_bytes = (int)((int64_t)a.N * a.Hi * a.Wi * Ci * 2);
+  const int filt_bytes = (int)((int64_t)a.Co * ph.ldb * 2);
+  constexpr uint32_t OOB = 0x80000000u;
+  const int wm = wave / WN, wn = wave % WN;
+
+  // one wave's share: TM row tiles from row 32 * T0 of the tile
+  auto work = [&](auto tmc, int T0) {
+    constexpr int TM = decltype(tmc)::value;
+    // DMA roles, 8 rows of 128 bytes per instruction: IA of the activation's
+    // rows from arow0, IB of the filter's from wave * IB * 8; physical chunk
+    // lane%8 holds logical chunk (lane%8) ^ ((row/2)%8).
+    constexpr int IA = WN == 4 ? TM : 2 * TM, IB = BN / 64, Q = IA + IB;
+    const int arow0 = WN == 4 ? 32 * T0 + wn * TM * 8 : wave * IA * 8;
+    const int brow0 = wave * IB * 8;
+    // Per activation row: the byte offset of its tap-(0,0) pixel and, with
+    // CGEN, that pixel's row and column, else a mask of the taps inside the
+    // image as in igemm7_kernel.
+    uint32_t a_pix[IA], a_vm[IA], b_off[IB];
+    int b_lc[IB];
+    int a_ih[CGEN ? IA : 1], a_iw[CGEN ? IA : 1];
+    const uint32_t pix_bytes = (uint32_t)Ci * 2u;
+    const uint32_t row_bytes = (uint32_t)a.Wi * pix_bytes;
+    // the lane's logical chunk in a row (the same for every second instruction)
+    auto chunk = [&](int row) { return (lane & 7) ^ ((row >> 1) & 7); };
 #pragma unroll
-      for (int q = 0; q < RH; ++q) {
-        const int r = h * RH + q;
-        if (r < rows) {
-          const float d = to_f32(to_h16(stg[r * K::SP + c])) - Kc;
-          s1 += d;
-          s2 = __builtin_fmaf(d, d, s2);
+    for (int q = 0; q < IA; ++q) {
+      const int row = arow0 + q * 8 + (lane >> 3);
+      const int m = m0 + row;
+      a_pix[q] = 0;
+      a_vm[q] = 0;
+      if (CGEN) {
+        a_ih[q] = -(1 << 28);
+        a_iw[q] = 0;
+      }
+      if (m < M) {
+        const int img = m / HoWo;
+        const int rem = m - img * HoWo;
+        const int i = rem / ph.Wo;
+        const int j = rem - i * ph.Wo;
+        const int ih0 = i * a.stride_h - ph.pad_h;
+        const int iw0 = j * a.stride_w - ph.pad_w;
+        a_pix[q] = (uint32_t)((int64_t)img * a.Hi * a.Wi * Ci * 2) +
+                   (uint32_t)(((int64_t)ih0 * a.Wi + iw0) * Ci * 2);
+        if (CGEN) {
+          a_ih[q] = ih0;
+          a_iw[q] = iw0;
+        } else {
+          a_pix[q] += (uint32_t)chunk(row) * 16u;
+          for (int r = 0; r < ph.Rt; ++r)
+            for (int t = 0; t < ph.St; ++t)
+              if ((unsigned)(ih0 + r) < (unsigned)a.Hi && (unsigned)(iw0 + t) < (unsigned)a.Wi)
+                a_vm[q] |= 1u << (r * ph.St + t);
         }
       }
-      if (CW < 64) {  // two lanes per column: rows 0-15 and 16-31
-        s1 += __shfl_xor(s1, 32, 64);
-        s2 += __shfl_xor(s2, 32, 64);
+    }
+#pragma unroll
+    for (int q = 0; q < IB; ++q) {
+      const int row = brow0 + q * 8 + (lane >> 3);
+      const int n = n0 + row;
+      b_lc[q] = chunk(row) * 8;
+      b_off[q] = n < a.Co ? (uint32_t)n * (uint32_t)ph.ldb * 2u + (uint32_t)b_lc[q] * 2u : OOB;
+    }
+    // k-step state.  Uniform: channel base, tap, and the byte offsets of the
+    // tap's pixel and of the step in a filter row.  CGEN: the step's first
+    // element and, for the lane's chunk in even and in odd instructions, its tap
+    // row, tap column and channel
+    int cb = 0, tap = 0, ts = 0, k0 = 0;
+    uint32_t tap_off = 0, b_step = 0;
+    int gr[2], gt[2], gc[2];
+    const int St = ph.St > 0 ? ph.St : 1;  // (a phase may have no tap)
+    const int inv_c = CGEN ? (65536 + Ci - 1) / Ci : 0;
+    const int inv_s = CGEN ? (65536 + St - 1) / St : 0;
+    if (CGEN) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int kk = chunk(arow0 + h * 8 + (lane >> 3)) * 8;
+        const int t = kk / Ci;
+        gc[h] = kk - t * Ci;
+        gr[h] = t / St;
+        gt[h] = t - gr[h] * St;
       }
-      if (lane < CW) {
-        bst[wn][band][0][c] = Kc;
-        bst[wn][band][1][c] = s1;
-        bst[wn][band][2][c] = s2;
+    }
+    // DMA q = 0 .. Q-1 of the next step (the activation's, then the filter's)
+    auto dma = [&](char* buf, int q) {
+      if (q < IA) {
+        const __amdgpu_buffer_rsrc_t rs_a = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<h16*>(a.act), (short)0, act_bytes, 0x00020000);
+        char* dst = buf + (arow0 + q * 8) * 128;
+        if (CGEN) {
+          const int r = gr[q & 1], t = gt[q & 1], c = gc[q & 1];
+          const bool v = taps > 0 && r < ph.Rt && (unsigned)(a_ih[q] + r) < (unsigned)a.Hi &&
+                         (unsigned)(a_iw[q] + t) < (unsigned)a.Wi;
+          const uint32_t addr = pin_v(a_pix[q] + (uint32_t)r * row_bytes +
+                                      (uint32_t)t * pix_bytes + (uint32_t)c * 2u);
+          dma16(rs_a, dst, v ? addr : OOB);
+        } else {
+          const uint32_t bit = cb < Ci ? 1u << tap : 0u;
+          const uint32_t addr = pin_v(a_pix[q] + tap_off + (uint32_t)cb * 2u);
+          dma16(rs_a, dst, (a_vm[q] & bit) ? addr : OOB);
+        }
+      } else {
+        const __amdgpu_buffer_rsrc_t rs_b = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<h16*>(ph.filt), (short)0, filt_bytes, 0x00020000);
+        char* dst = buf + BM * 128 + (brow0 + (q - IA) * 8) * 128;
+        if (CGEN) {
+          dma16(rs_b, dst, k0 + b_lc[q - IA] < Kg ? b_off[q - IA] + (uint32_t)k0 * 2u : OOB);
+        } else {
+          const uint32_t boff = cb < Ci ? b_step + (uint32_t)cb * 2u : 0x40000000u;
+          dma16(rs_b, dst, b_off[q - IA] + boff);
+        }
       }
-      if (lane == 0 && wn == 0) bcnt[band] = rows;
+    };
+    auto advance = [&]() {
+      if (CGEN) {
+        k0 += 64;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          gc[h] += 64;
+          if (Ci >= 64) {  // at most one tap further
+            const bool w = gc[h] >= Ci;
+            gc[h] -= w ? Ci : 0;
+            gt[h] += w ? 1 : 0;
+            const bool w2 = gt[h] == St;
+            gt[h] = w2 ? 0 : gt[h];
+            gr[h] += w2 ? 1 : 0;
+          } else {
+            // gc < 128 and gt < St + 16 <= 80: the quotients by products with
+            // the reciprocals rounded up, exact in this range
+            const int nt = (gc[h] * inv_c) >> 16;
+            gc[h] -= nt * Ci;
+            gt[h] += nt;
+            const int nr = (gt[h] * inv_s) >> 16;
+            gt[h] -= nr * St;
+            gr[h] += nr;
+          }
+        }
+        return;
+      }
+      b_step += pix_bytes;
+      if (++ts == ph.St) {
+        ts = 0;
+        tap_off += row_bytes - (uint32_t)(ph.St - 1) * pix_bytes;
+      } else {
+        tap_off += pix_bytes;
+      }
+      if (++tap == taps) {
+        tap = 0;
+        tap_off = 0;
+        b_step = 0;
+        cb += 64;
+      }
+    };
+
+    const int swz = (lrow >> 1) & 7;
+    floatx16 acc[TM];
+#pragma unroll
+    for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[tm][e] = 0.0f;
+    half8 af[2][TM], bf[2];
+    auto fetch = [&](const char* buf, int ks, half8 (&fa)[TM], half8& fb) {
+      const int pos = ((ks * 2 + lhi) ^ swz) * 16;
+      fb = *reinterpret_cast<const half8*>(buf + BM * 128 + (wn * 32 + lrow) * 128 + pos);
+#pragma unroll
+      for (int tm = 0; tm < TM; ++tm)
+        fa[tm] = *reinterpret_cast<const half8*>(buf + ((T0 + tm) * 32 + lrow) * 128 + pos);
+    };
+    auto mma = [&](const half8 (&fa)[TM], const half8& fb) {
+#pragma unroll
+      for (int tm = 0; tm < TM; ++tm) acc[tm] = mfma32x32x16(fb, fa[tm], acc[tm]);
+    };
+
+    const int KT = (Kg + 63) / 64;
+#pragma unroll
+    for (int s = 0; s < S - 1; ++s) {
+#pragma unroll
+      for (int q = 0; q < Q; ++q) dma(lds + s * K::STAGE, q);
+      advance();
+    }
+    constexpr int WAIT = (0x0 << 8) | (0x7 << 4) | (Q & 0xF) | ((Q >> 4) << 14);
+    __builtin_amdgcn_s_waitcnt(WAIT);
+    bare_barrier();
+    fetch(lds, 0, af[0], bf[0]);
+    int rd = 0, wr = S - 1;
+    for (int kt = 0; kt < KT; ++kt) {
+      // stage kt+2 goes into the buffer that step kt-1 freed, a few DMAs per
+      // sub-step (kept there by the scheduling barriers)
+      const char* cur = lds + rd * K::STAGE;
+      char* nxt = lds + wr * K::STAGE;
+      constexpr int P = (Q + 2) / 3;
+      fetch(cur, 1, af[1], bf[1]);
+#pragma unroll
+      for (int q = 0; q < P; ++q) dma(nxt, q);
+      mma(af[0], bf[0]);
+      __builtin_amdgcn_sched_barrier(0);
+      fetch(cur, 2, af[0], bf[0]);
+#pragma unroll
+      for (int q = P; q < (2 * P < Q ? 2 * P : Q); ++q) dma(nxt, q);
+      mma(af[1], bf[1]);
+      __builtin_amdgcn_sched_barrier(0);
+      fetch(cur, 3, af[1], bf[1]);
+#pragma unroll
+      for (int q = 2 * P; q < Q; ++q) dma(nxt, q);
+      mma(af[0], bf[0]);
+      advance();
+      __builtin_amdgcn_sched_barrier(0);
+      // this wave's reads of the stage are complete and its part of stage
+      // kt+1 has landed: publish it, and free this stage's buffer
+      __builtin_amdgcn_s_waitcnt(WAIT);
+      bare_barrier();
+      rd = rd + 1 == S ? 0 : rd + 1;
+      wr = wr + 1 == S ? 0 : wr + 1;
+      fetch(lds + rd * K::STAGE, 0, af[0], bf[0]);
+      mma(af[1], bf[1]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();  // every wave's stages have landed and been read
+    // the tile into LDS: row r, 16-byte chunks swizzled by the row
+#pragma unroll
+    for (int tm = 0; tm < TM; ++tm) {
+      const int r = (T0 + tm) * 32 + lrow;
+      float v[16];
+#pragma unroll
+      for (int e = 0; e < 16; ++e) v[e] = acc[tm][e];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        lane_half_swap(v[q], v[4 + q]);
+        lane_half_swap(v[8 + q], v[12 + q]);
+      }
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int c = wn * 4 + 2 * h + lhi;  // 8-channel chunk of the row
+        const float* w = v + h * 8;
+        if (ADD) {
+#pragma unroll
+          for (int j = 0; j < 2; ++j)
+            *reinterpret_cast<float4*>(lds + r * (BN * 4) +
+                                       (((2 * c + j) ^ (r & (2 * CPR - 1))) << 4)) =
+                make_float4(w[4 * j], w[4 * j + 1], w[4 * j + 2], w[4 * j + 3]);
+        } else {
+          V8 o;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) o.h[e] = to_h16(w[e]);
+          *reinterpret_cast<V8*>(lds + r * (BN * 2) + ((c ^ (r & (CPR - 1))) << 4)) = o;
+        }
+      }
+    }
+  };
+  if (WN == 2)
+    work(std::integral_constant<int, TA>(), wm * TA);
+  else if (wm == 0)
+    work(std::integral_constant<int, TA>(), 0);
+  else
+    work(std::integral_constant<int, TB>(), TA);
+  __syncthreads();
+
+  // whole rows out: thread = chunk tid % CPR of rows tid / CPR, + RPP, ...
+  constexpr int NP = BM / RPP;
+  const int c = tid % CPR;
+  const int n = n0 + c * 8;
+  const bool live = n < a.Co;
+  const bool whole = n + 8 <= a.Co && a.ldo % 8 == 0;  // 16-byte stores
+  const bool dense = a.os_h == 1 && a.os_w == 1;       // output row m is pixel m
+  float s1[8], s2[8];
+  V8 kv;
+  if (STATS) {
+    kv = *reinterpret_cast<const V8*>(lds + (c << 4));  // the tile's first row
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      s1[e] = 0.0f;
+      s2[e] = 0.0f;
+    }
+  }
+  // element offset of row i's pixel in the output, and in the addend (-1: +0)
+  auto out_row = [&](int m, int64_t& orow, int64_t& arow) {
+    orow = (int64_t)m * a.ldo;
+    arow = orow;
+    if (dense && a.astride <= 1) return;
+    const int img = m / HoWo;
+    const int rem = m - img * HoWo;
+    const int i = rem / ph.Wo;
+    const int oh = i * a.os_h + ph.oph, ow = (rem - i * ph.Wo) * a.os_w + ph.opw;
+    orow = ((int64_t)(img * a.OH + oh) * a.OW + ow) * a.ldo;
+    arow = ADD ? addend_row(a, img, oh, ow) : 0;
+  };
+  V8 adv[ADD ? NP : 1];
+  if (ADD) {  // every addend load in flight before the first is used
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+      const int m = m0 + tid / CPR + RPP * i;
+      adv[i] = zero8();
+      if (m < M && whole) {
+        int64_t orow, arow;
+        out_row(m, orow, arow);
+        if (arow >= 0) adv[i] = addend8(a, arow + n);
+      }
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < NP; ++i) {
+    const int r = tid / CPR + RPP * i;
+    const int m = m0 + r;
+    V8 o;
+    float w[8];
+    if (ADD) {
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const float4 f = *reinterpret_cast<const float4*>(
+            lds + r * (BN * 4) + (((2 * c + j) ^ (r & (2 * CPR - 1))) << 4));
+        w[4 * j] = f.x;
+        w[4 * j + 1] = f.y;
+        w[4 * j + 2] = f.z;
+        w[4 * j + 3] = f.w;
+      }
+    } else {
+      o = *reinterpret_cast<const V8*>(lds + r * (BN * 2) + ((c ^ (r & (CPR - 1))) << 4));
+    }
+    if (m >= M || !live) continue;
+    int64_t orow, arow;
+    out_row(m, orow, arow);
+    if (whole) {
+      if (ADD) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o.h[e] = to_h16(w[e] + to_f32(adv[i].h[e]));
+      }
+      store16(a.out + orow + n, o);
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        if (n + e < a.Co) {
+          if (ADD) o.h[e] = to_h16(w[e] + (arow >= 0 ? addend1(a, arow + n + e) : 0.0f));
+          a.out[orow + n + e] = o.h[e];
+        }
+      }
+    }
+    if (STATS) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float d = to_f32(o.h[e]) - to_f32(kv.h[e]);
+        s1[e] += d;
+        s2[e] = __builtin_fmaf(d, d, s2[e]);
+      }
+    }
+  }
+  if (STATS) {
+    // lanes l, l + CPR, l + 2*CPR, ... of a wave hold one chunk; then the waves
+#pragma unroll
+    for (int off = CPR; off < 64; off *= 2)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        s1[e] += __shfl_xor(s1[e], off, 64);
+        s2[e] += __shfl_xor(s2[e], off, 64);
+      }
+    float* red = reinterpret_cast<float*>(lds + K::EPI);  // [wave][2][BN]
+    if (lane < CPR) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        red[(wave * 2 + 0) * BN + c * 8 + e] = s1[e];
+        red[(wave * 2 + 1) * BN + c * 8 + e] = s2[e];
+      }
     }
     __syncthreads();
-  }
-  if (STATS && tid < WN * CW && bcnt[0] > 0) {
-    // one record per 128-row tile: the bands re-based on the first band's K
-    // (differences of two samples: no cancellation), in row order
-    const int h = tid / CW, c = tid % CW;
-    const int col = n0 + h * CW + c;
-    if (col < a.Co) {
-      const float K0 = bst[h][0][0][c];
+    if (tid < BN && n0 + tid < a.Co) {
       float S1 = 0.0f, S2 = 0.0f;
 #pragma unroll
-      for (int w = 0; w < NB; ++w) {
-        if (bcnt[w] == 0) break;
-        const float nw = (float)bcnt[w];
-        const float d = bst[h][w][0][c] - K0;
-        const float t1 = bst[h][w][1][c];
-        S1 += __builtin_fmaf(nw, d, t1);
-        S2 += __builtin_fmaf(nw * d, d, __builtin_fmaf(2.0f * d, t1, bst[h][w][2][c]));
+      for (int w = 0; w < 8; ++w) {
+        S1 += red[(w * 2 + 0) * BN + tid];
+        S2 += red[(w * 2 + 1) * BN + tid];
       }
-      float* rec = a.stat + (int64_t)(m0 / 128) * 3 * a.Co + col;
-      rec[0] = K0;
+      float* rec = a.stat + (int64_t)tm_ * 3 * a.Co + n0 + tid;
+      rec[0] = to_f32(*reinterpret_cast<const h16*>(lds + tid * 2));
       rec[a.Co] = S1;
       rec[2 * a.Co] = S2;
     }
@@ -1624,10 +1724,7 @@ hipError_t launch_cfg7(const IgemmArgs& a0, hipStream_t st) {
   dim3 grid(ceil_div(maxM, K::BM), ceil_div(a0.Co, K::BN), a0.nphase);
   IgemmArgs a = a0;
   a.gn = xcd_group(a, grid.y);
-  if (a.stat)
-    hipLaunchKernelGGL((igemm7_kernel<TM, TN, WM, WN, S, true>), grid, dim3(256), 0, st, a);
-  else
-    hipLaunchKernelGGL((igemm7_kernel<TM, TN, WM, WN, S, false>), grid, dim3(256), 0, st, a);
+  hipLaunchKernelGGL((igemm7_kernel<TM, TN, WM, WN, S>), grid, dim3(256), 0, st, a);
   return hipGetLastError();
 }
 
@@ -1644,6 +1741,36 @@ hipError_t launch_cfg4(const IgemmArgs& a0, hipStream_t st) {
   IgemmArgs a = a0;
   a.gn = xcd_group(a, grid.y);
   hipLaunchKernelGGL((igemm4_kernel<TM, TN>), grid, dim3(256), 0, st, a);
+  return hipGetLastError();
+}
+
+template <int WN, int TA, int TB>
+hipError_t launch_cfg8(const IgemmArgs& a0, hipStream_t st) {
+  using K = Cfg8<WN, TA, TB>;
+  int maxM = 0;
+  for (int p = 0; p < a0.nphase; ++p) maxM = max(maxM, a0.N * a0.ph[p].Ho * a0.ph[p].Wo);
+  if (maxM == 0 || a0.nphase == 0) return hipSuccess;
+  dim3 grid(ceil_div(maxM, K::BM), ceil_div(a0.Co, K::BN), a0.nphase);
+  IgemmArgs a = a0;
+  a.gn = xcd_group(a, grid.y);
+  bool gen = a.Ci % 64 != 0;
+  for (int p = 0; p < a.nphase; ++p) gen = gen || a.ph[p].Rt * a.ph[p].St > 32;
+#define FP16K_L8(STATS, ADD)                                                                    \
+  do {                                                                                          \
+    if (gen)                                                                                    \
+      hipLaunchKernelGGL((igemm8_kernel<WN, TA, TB, STATS, ADD, true>), grid, dim3(512), 0, st, \
+                         a);                                                                    \
+    else                                                                                        \
+      hipLaunchKernelGGL((igemm8_kernel<WN, TA, TB, STATS, ADD, false>), grid, dim3(512), 0,    \
+                         st, a);                                                                \
+  } while (0)
+  if (a.stat)
+    FP16K_L8(true, false);
+  else if (a.addend)
+    FP16K_L8(false, true);
+  else
+    FP16K_L8(false, false);
+#undef FP16K_L8
   return hipGetLastError();
 }
 
@@ -1731,21 +1858,6 @@ hipError_t launch_pw(const IgemmArgs& a, hipStream_t st) {
     }
   } else
     hipLaunchKernelGGL((pw_kernel<CI, BN, false, false, false>), grid, dim3(256), 0, st, a, ntiles);
-  return hipGetLastError();
-}
-
-template <int BM, int BN, int WM, int WN, int BK>
-hipError_t launch_cfg(const IgemmArgs& a0, hipStream_t st) {
-  int maxM = 0;
-  for (int p = 0; p < a0.nphase; ++p) {
-    const int m = a0.N * a0.ph[p].Ho * a0.ph[p].Wo;
-    if (m > maxM) maxM = m;
-  }
-  if (maxM == 0 || a0.nphase == 0) return hipSuccess;
-  dim3 grid(ceil_div(maxM, BM), ceil_div(a0.Co, BN), a0.nphase);
-  IgemmArgs a = a0;
-  a.gn = xcd_group(a, grid.y);
-  hipLaunchKernelGGL((igemm_kernel<BM, BN, WM, WN, BK>), grid, dim3(256), 0, st, a);
   return hipGetLastError();
 }
 
@@ -1925,94 +2037,133 @@ __global__ __launch_bounds__(512) void stem_kernel(const IgemmArgs a, int ntiles
 
 namespace {
 
-enum class IgemmKind { kLds, kDirect, kDma, kPointwise, k3x3 };
+// Tile of the wide kernel for this problem: the least of
+//   rounds * (100 + BM * BN / 128),  rounds = ceil(tiles / 256 CUs),
+// over the tile shapes.  (One workgroup alone on its CU takes 0.19 us plus 1.9
+// ns per row per k-step at BN = 128, measured at 64 to 256 rows, so its time
+// is proportional to 100 + rows.  The best shape measured agrees on the
+// layers tried: batch 128, 14x14 256 -> 256 3x3 224 rows 32.4 us against 33.7
+// at 256 and 42.7 at 128; 28x28 128 -> 128 224 rows 39.5 against 42; 7x7 512 ->
+// 512 128 rows 36.5 against 40.2 at 160; batch 32, 7x7 2048 -> 512 64 rows 12.7
+// against 16.4 at 128.)  Up to 64 channels the tiles are 64 channels wide, or
+// 64 rows x 128 where that gives every tile a CU of its own.
+struct WideTile {
+  int wn, ta, tb;
+  int rows() const { return wn == 4 ? 32 * (ta + tb) : 128 * ta; }
+};
+WideTile wide_choice(const IgemmArgs& a) {
+  static constexpr WideTile kTiles[] = {{4, 1, 1}, {4, 2, 2}, {4, 3, 2}, {4, 3, 3}, {4, 4, 3},
+                                        {4, 4, 4}, {2, 1, 1}, {2, 2, 2}};
+  WideTile best = kTiles[0];
+  int64_t cost = INT64_MAX;
+  for (const WideTile& t : kTiles) {
+    if (t.wn == 2 && a.Co > 64) continue;
+    if (t.wn == 4 && a.Co <= 64 && t.ta > 1) continue;
+    if (t.rows() < 128 && (int64_t)a.N * a.ph[0].Ho * a.ph[0].Wo > kStatSmallRows) continue;
+    int64_t tiles = 0;
+    for (int p = 0; p < a.nphase; ++p)
+      tiles += ceil_div(a.N * a.ph[p].Ho * a.ph[p].Wo, t.rows());
+    tiles *= ceil_div(a.Co, 32 * t.wn);
+    const int64_t c = ceil_div64(tiles, 256) * (100 + t.rows() * t.wn / 4);
+    if (c < cost) {
+      cost = c;
+      best = t;
+    }
+  }
+  return best;
+}
 
-// Kernel choice per problem (measured on MI355X over the ResNet-50 shapes at
-// batch 32 and 128): the pointwise kernel for 1x1 filters over 64 or 128
-// channels with 128+ output channels; the DMA-staged kernel for reductions of
-// 512 and more (every 3x3 layer, the 1x1 layers with 512+ input channels);
-// below that the register-direct kernel for short reductions or small M,
-// else the LDS-staged one.  All four give identical bits.
+hipError_t launch_wide(const IgemmArgs& a, hipStream_t st) {
+  const WideTile t = wide_choice(a);
+  if (t.wn == 2) return t.ta == 1 ? launch_cfg8<2, 1, 1>(a, st) : launch_cfg8<2, 2, 2>(a, st);
+  switch (t.ta + t.tb) {
+    case 2: return launch_cfg8<4, 1, 1>(a, st);
+    case 4: return launch_cfg8<4, 2, 2>(a, st);
+    case 5: return launch_cfg8<4, 3, 2>(a, st);
+    case 6: return launch_cfg8<4, 3, 3>(a, st);
+    case 7: return launch_cfg8<4, 4, 3>(a, st);
+    default: return launch_cfg8<4, 4, 4>(a, st);
+  }
+}
+
+enum class IgemmKind { kWide, kDirect, kDma, kPointwise, k3x3 };
+
+// Kernel choice per problem, each line drawn where the kernels on its two
+// sides measured alike (us per call on MI355X, NHWC, the wide kernel's time
+// second):
+//  - the 3x3 64-channel kernel from 256 of its tiles on (one per CU): batch
+//    128 of 56x56 45.7 against 55.9, batch 32 18.2 against 18.9, batch 2
+//    9.6 against 6.0;
+//  - the pointwise kernel for 1x1 filters over 64 or 128 channels (256 without
+//    an addend) with a dense output of 128+ channels, from 65,536 output rows
+//    on: 28x28 128 -> 512 at batch 128 34.9 against 43.9, at batch 32 28.3
+//    against 14.8; 56x56 256 -> 128 69 against 77; 14x14 256 -> 1024 at batch
+//    128 (25,088 rows) 33.9 against 32-34.6;
+//  - the register-direct kernel for reductions up to 256 over 131,072 rows or
+//    more in one phase (56x56 256 -> 64 at batch 128 44.4 against 45.7, at
+//    batch 32, 100,352 rows, 16.7 against 14.2), and for the short phases (up
+//    to 512) of large strided data gradients;
+//  - the 128 x 128 DMA-staged kernel, two workgroups per CU, for the longer
+//    phases of strided data gradients while they are short against a
+//    workgroup's start and end (up to 1,023) and more than 512 tiles: 56x56
+//    128 -> 128 3x3 stride 2 at batch 128 70 against 71-78, at batch 32 25.2
+//    against 21.6;
+//  - the wide kernel everywhere else.
+// All give the sums of the same products in float32; the wide kernel's are in
+// another order (see there) where the channels exceed 64.
 IgemmKind igemm_kind(const IgemmArgs& a) {
-  if (c3_tiles_per_image(a) > 0) return IgemmKind::k3x3;
+  if ((int64_t)a.N * c3_tiles_per_image(a) >= 256) return IgemmKind::k3x3;
+  int maxK = 0, maxT = 0;
+  int64_t rows = 0;
+  for (int p = 0; p < a.nphase; ++p) {
+    const int t = a.ph[p].Rt * a.ph[p].St;
+    rows += (int64_t)a.N * a.ph[p].Ho * a.ph[p].Wo;
+    if (t * a.Ci > maxK) maxK = t * a.Ci;
+    if (t > maxT) maxT = t;
+  }
+  const int64_t act = (int64_t)a.N * a.Hi * a.Wi * a.Ci * 2;
   {
-    // a 1x1 filter over 64 or 128 channels (or 256 without an addend) with a
-    // dense output of 128+ channels: the pointwise kernel.  (Over 256 channels
-    // its workgroups, one per CU walking a fixed share of the tiles, ran the
-    // conv4_x block inputs' data gradients 48 us against 58 alone, but 82-89
-    // against 66 in the training step, beside the weight gradients on the
-    // second stream: the register-direct kernel's one-tile workgroups share
-    // the CUs better.)
     const IgemmPhase& p = a.ph[0];
-    const int64_t act = (int64_t)a.N * a.Hi * a.Wi * a.Ci * 2;
     const bool ci_ok = a.Ci == 64 || a.Ci == 128 || (a.Ci == 256 && !a.addend);
     if (a.nphase == 1 && p.Rt == 1 && p.St == 1 && p.pad_h == 0 && p.pad_w == 0 &&
         p.oph == 0 && p.opw == 0 && a.os_h == 1 && a.os_w == 1 && a.OH == p.Ho &&
         a.OW == p.Wo && ci_ok && p.ldb == a.Ci && a.Co >= 128 &&
-        a.Co % 8 == 0 && a.ldo % 8 == 0 && act < ((int64_t)1 << 31))
+        a.Co % 8 == 0 && a.ldo % 8 == 0 && act < ((int64_t)1 << 31) && rows >= 65536)
       return IgemmKind::kPointwise;
   }
-  int maxM = 0, maxK = 0, maxT = 0;
-  int64_t maxF = 0;
-  for (int p = 0; p < a.nphase; ++p) {
-    const int m = a.N * a.ph[p].Ho * a.ph[p].Wo;
-    const int t = a.ph[p].Rt * a.ph[p].St;
-    const int64_t f = (int64_t)a.Co * a.ph[p].ldb * 2;
-    if (m > maxM) maxM = m;
-    if (t * a.Ci > maxK) maxK = t * a.Ci;
-    if (t > maxT) maxT = t;
-    if (f > maxF) maxF = f;
+  const int64_t tiles = ceil_div64(rows, 128) * ceil_div(a.Co, a.Co <= 64 ? 64 : 128);
+  if (a.nphase > 1 && tiles > 512 && maxK < 1024) {
+    if (a.Ci % 64 == 0 && maxK >= 576 && maxT <= 32) return IgemmKind::kDma;
+    if (a.Ci % 32 == 0 && maxK <= 512) return IgemmKind::kDirect;
   }
-  const int64_t act = (int64_t)a.N * a.Hi * a.Wi * a.Ci * 2;
-  // (a 512-long 1x1 reduction is faster on it too, except in a strided data
-  // gradient, whose empty phases favour the register-direct kernel)
-  const int kmin = a.nphase > 1 ? 576 : 512;
-  if (a.Ci % 64 == 0 && maxK >= kmin && maxT <= 32 && act < ((int64_t)1 << 31) &&
-      maxF <= ((int64_t)1 << 30))
-    return IgemmKind::kDma;
-  if (a.Ci % 32 == 0 && (maxK <= 512 || maxM <= 8192)) return IgemmKind::kDirect;
-  return IgemmKind::kLds;
+  if (a.nphase == 1 && a.Ci % 32 == 0 && maxK <= 256 && rows >= 131072) return IgemmKind::kDirect;
+  return IgemmKind::kWide;
 }
 
 }  // namespace
 
 bool igemm_stats_pay(const IgemmArgs& a) {
-  // Measured on every ResNet-50 conv -> BN shape at batch 128 (fused call vs
-  // convolution + the BN's own statistics pass): the 3x3 64-channel kernel
-  // without statistics beats the DMA-staged kernel with them by more than the
-  // statistics pass costs (97.7 vs 78.6 us), and so does the DMA-staged
-  // kernel's statistics-free form from 100,352 output rows on (the 28x28
-  // layers, 2-5 us); below that, and on the other kernels, fusing pays.
-  if (!igemm_takes_stats(a)) return false;
-  IgemmArgs b = a;
-  b.stat = nullptr;
-  if (igemm_kind(b) == IgemmKind::k3x3) return false;
-  b.stat = reinterpret_cast<float*>(1);
-  return !(igemm_kind(b) == IgemmKind::kDma && (int64_t)a.N * a.OH * a.OW >= 100352);
+  // the 3x3 64-channel kernel takes no statistics, and beats the others with
+  // them by more than a separate statistics pass costs
+  return igemm_kind(a) != IgemmKind::k3x3;
 }
 
 bool igemm_takes_apply(const IgemmArgs& a) {
   // the pointwise kernel over 64 input channels: a second pass that
   // recomputes y from x (a quarter of y's bytes) and writes z in place of the
   // BN apply's read of y
-  IgemmArgs b = a;
-  b.stat = nullptr;
-  return !a.addend && !a.amask && a.Ci == 64 && igemm_kind(b) == IgemmKind::kPointwise;
+  return !a.addend && !a.amask && a.Ci == 64 && igemm_kind(a) == IgemmKind::kPointwise;
+}
+
+int igemm_stat_rows(const IgemmArgs& a) {
+  return igemm_kind(a) == IgemmKind::kWide ? wide_choice(a).rows() : 128;
 }
 
 int igemm_stat_records(const IgemmArgs& a) {
-  const int ntiles = ceil_div(a.N * a.ph[0].Ho * a.ph[0].Wo, 128);
+  const int ntiles = ceil_div(a.N * a.ph[0].Ho * a.ph[0].Wo, igemm_stat_rows(a));
   return igemm_kind(a) == IgemmKind::kPointwise
              ? pw_row_groups(ntiles, a.Ci, true, ceil_div(a.Co, pw_tile_n(a)))
              : ntiles;
-}
-
-bool igemm_takes_stats(const IgemmArgs& a) {
-  // the kernel that would run with statistics requested (the 3x3 kernel
-  // leaves them to the DMA-staged one)
-  IgemmArgs b = a;
-  b.stat = reinterpret_cast<float*>(1);
-  return igemm_kind(b) != IgemmKind::kLds;
 }
 
 // ---- dense GEMM with a split reduction ------------------------------------------
@@ -2112,16 +2263,8 @@ hipError_t launch_igemm(const IgemmArgs& a, hipStream_t st) {
     return hipGetLastError();
   }
   switch (igemm_kind(a)) {
-    case IgemmKind::kDma: {
-      // two stages (two workgroups per CU) unless the grid fits the 256 CUs
-      // once, where a third stage of prefetch costs no occupancy
-      int maxM = 0;
-      for (int p = 0; p < a.nphase; ++p) maxM = max(maxM, a.N * a.ph[p].Ho * a.ph[p].Wo);
-      const bool narrow = a.Co <= 64;
-      const int64_t wgs = (int64_t)ceil_div(maxM, 128) * ceil_div(a.Co, narrow ? 64 : 128) * a.nphase;
-      if (narrow) return wgs <= 256 ? launch_cfg7<2, 1, 2, 2, 3>(a, st) : launch_cfg7<2, 1, 2, 2, 2>(a, st);
-      return wgs <= 256 ? launch_cfg7<2, 2, 2, 2, 3>(a, st) : launch_cfg7<2, 2, 2, 2, 2>(a, st);
-    }
+    case IgemmKind::kDma:
+      return a.Co <= 64 ? launch_cfg7<2, 1, 2, 2, 2>(a, st) : launch_cfg7<2, 2, 2, 2, 2>(a, st);
     case IgemmKind::kDirect:
       return a.Co <= 64 ? launch_cfg4<1, 2>(a, st) : launch_cfg4<1, 4>(a, st);
     case IgemmKind::k3x3:
@@ -2133,7 +2276,7 @@ hipError_t launch_igemm(const IgemmArgs& a, hipStream_t st) {
       return launch_pw<256, 128>(a, st);
     }
     default:
-      return a.Co <= 64 ? launch_cfg<128, 64, 4, 1, 64>(a, st) : launch_cfg<128, 128, 2, 2, 64>(a, st);
+      return launch_wide(a, st);
   }
 }
 

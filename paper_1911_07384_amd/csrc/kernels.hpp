@@ -60,9 +60,9 @@ struct IgemmArgs {
   int nphase;
   IgemmPhase ph[4];
   // Optional statistics of the rounded output for a following BN (single
-  // phase, Co % 8 == 0, no addend, and a kernel that takes them, see
-  // igemm_takes_stats): nb = igemm_stat_records records; record j covers the
-  // 128-row tiles j, j + nb, j + 2nb, ... of the output rows and holds, per
+  // phase, Co % 8 == 0, no addend): nb = igemm_stat_records records; record j
+  // covers the tiles j, j + nb, j + 2nb, ... of igemm_stat_rows output rows
+  // each and holds, per
   // channel c, a shift K (one of its values) and the sums of (y - K) and
   // (y - K)^2 over its rows, at stat[(j * 3 + q) * Co + c], q = 0, 1, 2.
   float* stat;
@@ -108,15 +108,15 @@ bool igemm_stats_pay(const IgemmArgs& a);
 // problem (with statistics when a.stat is set).
 bool stem_conv_ok(const IgemmArgs& a);
 hipError_t launch_stem(const IgemmArgs& a, hipStream_t st);
-// Whether the kernel launch_igemm picks for this problem can take the BN
-// statistics (IgemmArgs::stat) in its epilogue.
-bool igemm_takes_stats(const IgemmArgs& a);
 // Whether launch_igemm can apply a following BN in the epilogue of this
 // problem (IgemmArgs::bn_stats; the problem without stats, addend or mask).
 bool igemm_takes_apply(const IgemmArgs& a);
-// The number of statistics records the kernel picked for this problem writes
-// (one per 128-row tile, or fewer where a workgroup sums several tiles);
-// never more than the tiles.
+// Rows of one statistics tile of the kernel picked for this problem (64 to
+// 256, 64 only for problems of at most kStatSmallRows output rows), and the
+// number of records it writes (one per tile, or fewer where a workgroup sums
+// several tiles).
+constexpr int64_t kStatSmallRows = 65536;
+int igemm_stat_rows(const IgemmArgs& a);
 int igemm_stat_records(const IgemmArgs& a);
 
 // Geometry of one stride phase (ph, pw) of the data gradient.  Output rows
@@ -210,13 +210,13 @@ hipError_t launch_bn_fwd(const BnArgs& a, const h16* x, const h16* gamma, const 
 size_t bn_keep_mask_bytes(const BnArgs& a);
 // Forward from the band records of a convolution epilogue (IgemmArgs::stat):
 // statistics, then the apply.  part: [nb][3][C] float32, record j over the
-// 128-row tiles j, j + nb, ...;
+// tiles j, j + nb, ... of `rows` rows each;
 // band_ws: bn_band_ws_bytes(C, nb) bytes of scratch for the per-slice sums.
 size_t bn_band_ws_bytes(int C, int nb);
 // The statistics alone from such records (mean [C], 1/sqrt(var + eps) [C]).
-hipError_t launch_bn_band_stats(const BnArgs& a, const float* part, int nb, void* band_ws,
+hipError_t launch_bn_band_stats(const BnArgs& a, const float* part, int nb, int rows, void* band_ws,
                                 float* stats, hipStream_t st);
-hipError_t launch_bn_fwd_bands(const BnArgs& a, const float* part, int nb, void* band_ws,
+hipError_t launch_bn_fwd_bands(const BnArgs& a, const float* part, int nb, int rows, void* band_ws,
                                const h16* x, const h16* gamma, const h16* beta, const h16* res,
                                h16* y, float* stats, uint8_t* mout, hipStream_t st);
 // mask (nullable): the ReLU mask the forward kept (no BN swap)
