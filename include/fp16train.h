@@ -214,9 +214,11 @@ fp16_status fp16_conv_wgrad(const fp16_conv_desc* desc, const fp16_t* x, const f
 /* fp16_conv_wgrad split over fewer pixel ranges, for a weight gradient that
  * runs beside other work on the device (the data-parallel backward of
  * Section 5.1 overlaps the weight gradients with the data gradients and BN
- * backwards on a second stream): the partial products aim at `workgroups`
- * workgroups in all, 1 <= workgroups <= 512, instead of the default 512 (two
- * per compute unit); 0 is the default, identical to fp16_conv_wgrad.  Fewer
+ * backwards on a second stream): the partial products take at most
+ * `workgroups` workgroups in all (or one per tile of the filter), 1 <=
+ * workgroups <= 512, instead of the default (one or two per compute unit, by
+ * the kernel; it is also the most); 0 is the default, identical to
+ * fp16_conv_wgrad.  Fewer
  * ranges mean fewer float32 partial sums written and re-read and more of the
  * device left to the other stream; the partial sums are added in a fixed
  * order as always, so results are deterministic for a given count (and

@@ -5,9 +5,8 @@
 //   col = (r, s, c) with c fastest (the KRSC filter row),
 //   X[pix][(r,s,c)] = x[image][p*sh - ph + r][q*sw - pw + s][c] (zero outside).
 // Both operands are channel-contiguous in memory but the reduction runs over
-// pixels, so each thread loads an 8-pixel x 8-channel block (eight 16-byte
-// loads), transposes it in registers with byte permutes, and writes eight
-// 16-byte channel rows into LDS.  MFMA operands are then 16-byte LDS reads.
+// pixels: they are DMA'd pixel-major into LDS and the MFMA operands come from
+// gfx950's transposing LDS read.
 //
 // The pixel range is split across workgroups (split-K).  Each split writes
 // its float32 partial tile to the workspace; a second kernel adds the splits
@@ -21,160 +20,10 @@
 namespace fp16k {
 namespace {
 
-constexpr int BKP = 64;         // pixels per k-step
-constexpr int LDP = BKP + 8;    // LDS row pitch (halves)
+constexpr int BKP = 64;  // pixels per k-step
 
-template <int BM, int BN, int WM, int WN>
-__global__ __launch_bounds__(256) void wgrad_kernel(const WgradArgs a) {
-  constexpr int WTM = BM / WM, WTN = BN / WN;
-  constexpr int TM = WTM / 32, TN = WTN / 32;
-  constexpr int NA = (BKP / 8) * (BM / 8);  // 8x8 blocks of the dy tile
-  constexpr int NB = (BKP / 8) * (BN / 8);  // 8x8 blocks of the x tile
-  static_assert(NA + NB <= 256, "one block per thread at most");
-  static_assert(NA % 64 == 0, "wave-uniform A/B split");
-  static_assert(WM * WN == 4 && TM >= 1 && TN >= 1, "tile shape");
-
-  __shared__ __attribute__((aligned(16))) h16 As[2][BM * LDP];
-  __shared__ __attribute__((aligned(16))) h16 Bs[2][BN * LDP];
-
-  const int Nw = a.R * a.S * a.C;
-  const int tiles_n = (Nw + BN - 1) / BN;
-  const int tile = blockIdx.x;
-  const int m0 = (tile / tiles_n) * BM;
-  const int n0 = (tile % tiles_n) * BN;
-  const int split = blockIdx.y;
-  const int64_t npix = (int64_t)a.N * a.P * a.Q;
-  const int64_t pbeg = (int64_t)split * a.pix_per_split;
-  int64_t pend = pbeg + a.pix_per_split;
-  if (pend > npix) pend = npix;
-
-  const int tid = threadIdx.x;
-  const bool is_a = tid < NA;
-  const bool is_b = !is_a && tid < NA + NB;
-  // block coordinates: pixel group pi (8 pixels), channel group ci (8 channels)
-  const int bidx = is_a ? tid : tid - NA;
-  const int pi = bidx % (BKP / 8);
-  const int ci = bidx / (BKP / 8);
-
-  // x column chunk of a B-thread: tap (r, s) and channel offset c
-  int br = 0, bs = 0, bc = 0;
-  bool bcol_ok = false;
-  if (is_b) {
-    const int col = n0 + ci * 8;
-    bcol_ok = col < Nw;
-    const int tap = bcol_ok ? col / a.C : 0;
-    bc = col - tap * a.C;
-    br = tap / a.S;
-    bs = tap - br * a.S;
-  }
-  const bool acol_ok = is_a && (m0 + ci * 8) < a.K;
-
-  V8 blk[8];
-  auto load_tile = [&](int64_t p0) {
-    const int64_t pix0 = p0 + pi * 8;
-    if (is_a) {
-#pragma unroll
-      for (int v = 0; v < 8; ++v) {
-        const int64_t pix = pix0 + v;
-        blk[v] = (acol_ok && pix < pend) ? load16(a.dy + pix * a.K + m0 + ci * 8) : zero8();
-      }
-    } else if (is_b) {
-      // decompose the first pixel, then step (q, p, image) incrementally
-      int64_t t = pix0;
-      int q = (int)(t % a.Q);
-      t /= a.Q;
-      int p = (int)(t % a.P);
-      int img = (int)(t / a.P);
-#pragma unroll
-      for (int v = 0; v < 8; ++v) {
-        const int ih = p * a.sh - a.ph + br;
-        const int iw = q * a.sw - a.pw + bs;
-        const bool ok = bcol_ok && (pix0 + v) < pend && (unsigned)ih < (unsigned)a.H &&
-                        (unsigned)iw < (unsigned)a.W;
-        blk[v] = ok ? load16(a.x + ((int64_t)(img * a.H + ih) * a.W + iw) * a.C + bc) : zero8();
-        if (++q == a.Q) {
-          q = 0;
-          if (++p == a.P) {
-            p = 0;
-            ++img;
-          }
-        }
-      }
-    }
-  };
-  auto store_tile = [&](int buf) {
-    if (!is_a && !is_b) return;
-    V8 tr[8];
-    transpose8x8(blk, tr);
-    h16* base = is_a ? &As[buf][0] : &Bs[buf][0];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) store16(base + (ci * 8 + j) * LDP + pi * 8, tr[j]);
-  };
-
-  const int wave = tid >> 6, lane = tid & 63;
-  const int wm = wave / WN, wn = wave % WN;
-  const int lrow = lane & 31, lk = (lane >> 5) * 8;
-
-  floatx16 acc[TM][TN];
-#pragma unroll
-  for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-    for (int tn = 0; tn < TN; ++tn)
-#pragma unroll
-      for (int e = 0; e < 16; ++e) acc[tm][tn][e] = 0.0f;
-
-  const int KT = pend > pbeg ? (int)((pend - pbeg + BKP - 1) / BKP) : 0;
-  if (KT > 0) {
-    load_tile(pbeg);
-    store_tile(0);
-  }
-  __syncthreads();
-  for (int kt = 0; kt < KT; ++kt) {
-    const int buf = kt & 1;
-    if (kt + 1 < KT) load_tile(pbeg + (int64_t)(kt + 1) * BKP);
-#pragma unroll
-    for (int ks = 0; ks < BKP / 16; ++ks) {
-      half8 af[TM], bf[TN];
-#pragma unroll
-      for (int tm = 0; tm < TM; ++tm)
-        af[tm] = *reinterpret_cast<const half8*>(
-            &As[buf][(wm * WTM + tm * 32 + lrow) * LDP + ks * 16 + lk]);
-#pragma unroll
-      for (int tn = 0; tn < TN; ++tn)
-        bf[tn] = *reinterpret_cast<const half8*>(
-            &Bs[buf][(wn * WTN + tn * 32 + lrow) * LDP + ks * 16 + lk]);
-#pragma unroll
-      for (int tm = 0; tm < TM; ++tm)
-#pragma unroll
-        for (int tn = 0; tn < TN; ++tn) {
-          acc[tm][tn] = mfma32x32x16(af[tm], bf[tn], acc[tm][tn]);
-        }
-    }
-    if (kt + 1 < KT) store_tile(buf ^ 1);
-    __syncthreads();
-  }
-
-  // float32 partial tile of this split
-  float* out = a.partial + (int64_t)split * a.K * Nw;
-#pragma unroll
-  for (int tm = 0; tm < TM; ++tm) {
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-      const int m = m0 + wm * WTM + tm * 32 + 8 * (e >> 2) + 4 * (lane >> 5) + (e & 3);
-      if (m >= a.K) continue;
-#pragma unroll
-      for (int tn = 0; tn < TN; ++tn) {
-        const int n = n0 + wn * WTN + tn * 32 + lrow;
-        if (n < Nw) out[(int64_t)m * Nw + n] = acc[tm][tn][e];
-      }
-    }
-  }
-}
-
-// ---- DMA-staged variant: no register transposes ------------------------------
-// For K a multiple of 64 and C a multiple of 8 (when C is not a multiple of
-// 64 -- the padded 3-channel stem -- each lane's 8-channel chunk carries its
-// own filter tap).  Each stage covers 64 pixels:
+// For K and C multiples of 8 (where C is not a multiple of 64, each lane's
+// 8-channel chunk carries its own filter tap).  Each stage covers 64 pixels:
 // the dy rows (BM channels) and the x patch rows (BN filter columns, 64 per
 // tap and channel block) are DMA'd pixel-major straight into LDS, in 8 KB
 // sub-tiles of 64 pixel rows x 128 bytes (16-byte chunks XOR-swizzled by
@@ -182,9 +31,8 @@ __global__ __launch_bounds__(256) void wgrad_kernel(const WgradArgs a) {
 // come from the transposing LDS read of gfx950 (ds_read_b64_tr_b16: within
 // each 16-lane group, lane b*4+a receives element a of the 8-byte rows that
 // lanes b, b+4, b+8 and b+12 address), two reads per operand.  S stages in a
-// ring, operand reads one k sub-step ahead, as in the implicit-GEMM kernel.
-// The k order (pixels) and the split plan are those of wgrad_kernel, so the
-// partial sums are the same.
+// ring, operand reads one k sub-step ahead, as in the implicit-GEMM kernels;
+// four waves, or eight with one workgroup per CU (see wgrad_choice).
 
 typedef short short4v __attribute__((ext_vector_type(4)));
 
@@ -224,20 +72,25 @@ __device__ __forceinline__ void lds_tie(half8& v) { __asm__ volatile("" : "+v"(v
 template <int BM, int BN, int WM, int WN, int S>
 struct WCfg7 {
   static constexpr int SA = BM / 64, SB = BN / 64;  // 64-channel sub-tiles
+  static constexpr int NW = WM * WN;                // waves: 4 or 8
   static constexpr int NI = (SA + SB) * 8;          // DMA instructions per stage
-  static constexpr int IW = NI / 4;                 // per wave
+  static constexpr int IW = NI / NW;                // per wave
+  static constexpr int H = 8 / NW;                  // pixel rows per lane and sub-tile
   static constexpr int STAGE = (SA + SB) * 8192;    // bytes
   static constexpr int WTM = BM / WM, WTN = BN / WN;
   static constexpr int TM = WTM / 32, TN = WTN / 32;
 };
 
 template <int BM, int BN, int WM, int WN, int S, bool CGEN = false>
-__global__ __launch_bounds__(256) void wgrad7_kernel(const WgradArgs a) {
+__global__ __launch_bounds__(64 * WM * WN) void wgrad7_kernel(const WgradArgs a) {
   using K = WCfg7<BM, BN, WM, WN, S>;
-  constexpr int SA = K::SA, SB = K::SB, IW = K::IW, TM = K::TM, TN = K::TN, WTM = K::WTM,
-                WTN = K::WTN;
-  static_assert(WM * WN == 4 && TM >= 1 && TN >= 1 && S >= 2, "tile shape");
+  constexpr int SA = K::SA, SB = K::SB, IW = K::IW, H = K::H, TM = K::TM, TN = K::TN,
+                WTM = K::WTM, WTN = K::WTN;
+  static_assert((K::NW == 4 || K::NW == 8) && TM >= 1 && TN >= 1 && S >= 2, "tile shape");
   static_assert(IW * (S - 1) < 64, "vmcnt range");
+  // with a third stage the next loads go out between the MFMAs of a step, a
+  // few per sub-step, instead of in a burst behind its barrier
+  constexpr bool SPREAD = S >= 3;
   __shared__ __attribute__((aligned(1024))) char lds[S * K::STAGE];
 
   const int Nw = a.R * a.S * a.C;
@@ -257,108 +110,109 @@ __global__ __launch_bounds__(256) void wgrad7_kernel(const WgradArgs a) {
   }
   const int m0 = (tile / tiles_n) * BM;
   const int n0 = (tile % tiles_n) * BN;
-  const int64_t npix = (int64_t)a.N * a.P * a.Q;
-  const int64_t pbeg = (int64_t)split * a.pix_per_split;
-  int64_t pend = pbeg + a.pix_per_split;
-  if (pend > npix) pend = npix;
-  const int KT = pend > pbeg ? (int)((pend - pbeg + 63) / 64) : 0;
+  const int npix = a.N * a.P * a.Q;  // < 2^30
+  const int pbeg = split * a.pix_per_split;
+  const int pend = npix - pbeg < a.pix_per_split ? npix : pbeg + a.pix_per_split;
+  const int KT = pend > pbeg ? (pend - pbeg + 63) / 64 : 0;
 
   const int tid = threadIdx.x;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   constexpr uint32_t OOB = 0x80000000u;
-  const int dy_bytes = (int)(npix * a.K * 2);
+  const int dy_bytes = (int)((int64_t)npix * a.K * 2);
   const int x_bytes = (int)((int64_t)a.N * a.H * a.W * a.C * 2);
 
-  // DMA roles: instruction i of this wave fills sub-tile i/2, pixel rows
-  // rb*8 .. rb*8+7 with rb = 4*(i%2) + wave; a lane covers pixel row
+  // DMA roles: instruction i of this wave fills sub-tile i/H, pixel rows
+  // rb*8 .. rb*8+7 with rb = 4*(i%H) + wave; a lane covers pixel row
   // rb*8 + lane/8 and physical chunk lane%8, holding logical chunk
   // (lane%8) ^ swz(row), swz(row) = 2*(row%4).  A transposing read takes
   // 32 bytes (chunks 2i, 2i+1) from each of 4 consecutive rows per 16-lane
   // group; with this swizzle the 4 rows' pairs land on distinct chunk
   // positions, and the two groups served together (the other channel
   // half) on the rest, so the reads are bank-conflict free.
-  int prow[2], img[2], pp[2], qq[2];
+  // Per pixel row: the next step's pixel (relative to pend), its output row
+  // and column as the input position of tap (0, 0), and the byte offsets of
+  // its chunk in dy and of tap (0, 0) in x (wrapping below zero in the
+  // padding): a DMA then costs an add and its range checks.
+  const int lc = (lane & 7) ^ (((lane >> 3) & 3) << 1);  // (rows 8 apart share it)
+  bool av[SA];  // the lane's chunk of each dy sub-tile is inside K
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    prow[h] = (4 * h + wave) * 8 + (lane >> 3);
-    const int64_t pix = pbeg + prow[h];
-    const int64_t PQ = (int64_t)a.P * a.Q;
-    img[h] = (int)(pix / PQ);
-    const int rem = (int)(pix - (int64_t)img[h] * PQ);
-    pp[h] = rem / a.Q;
-    qq[h] = rem - pp[h] * a.Q;
-  }
+  for (int u = 0; u < SA; ++u) av[u] = m0 + u * 64 + lc * 8 < a.K;
+  int left[H], ih0[H], iw0[H];
+  uint32_t dyo[H], xo[H];
   const int dq = 64 % a.Q, dp = (64 / a.Q) % a.P, dimg = 64 / (a.P * a.Q);
-  int lc[2];
+  const uint32_t pix_bytes = (uint32_t)a.C * 2u, row_bytes = (uint32_t)a.W * pix_bytes,
+                 img_bytes = (uint32_t)a.H * row_bytes;
 #pragma unroll
-  for (int h = 0; h < 2; ++h) lc[h] = (lane & 7) ^ ((prow[h] & 3) << 1);
-  // CGEN (C a multiple of 8 but not of 64): a 64-column block of the x patch
-  // spans several filter taps, so each lane's 8-channel chunk has a tap of its
-  // own; precomputed here (tap row, tap column, channel offset; -1 past Nw)
-  int gr[2][CGEN ? SB : 1], gt[2][CGEN ? SB : 1], gc[2][CGEN ? SB : 1];
-  if (CGEN) {
+  for (int h = 0; h < H; ++h) {
+    const int pix = pbeg + (4 * h + wave) * 8 + (lane >> 3);
+    const int PQ = a.P * a.Q;
+    const int img = pix / PQ;
+    const int rem = pix - img * PQ;
+    const int p = rem / a.Q, q = rem - p * a.Q;
+    left[h] = pend - pix;
+    ih0[h] = p * a.sh - a.ph;
+    iw0[h] = q * a.sw - a.pw;
+    dyo[h] = (uint32_t)pix * (uint32_t)a.K * 2u + (uint32_t)(m0 + lc * 8) * 2u;
+    xo[h] = (uint32_t)img * img_bytes + (uint32_t)ih0[h] * row_bytes +
+            (uint32_t)iw0[h] * pix_bytes;
+  }
+  // the filter tap of each x sub-tile (and its channel base): uniform; with
+  // CGEN (C a multiple of 8 but not of 64) a 64-column block spans several
+  // taps and each lane's 8-channel chunk has a tap of its own (none past Nw)
+  int tr[SB], ts[SB];
+  uint32_t to[SB];
+  bool tv[SB];
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
-#pragma unroll
-      for (int b = 0; b < SB; ++b) {
-        const int col = n0 + b * 64 + lc[h] * 8;
-        const int tap = col / a.C;
-        gc[h][b] = col < Nw ? col - tap * a.C : -1;
-        gr[h][b] = tap / a.S;
-        gt[h][b] = tap - gr[h][b] * a.S;
-      }
+  for (int b = 0; b < SB; ++b) {
+    const int col = n0 + b * 64 + (CGEN ? lc * 8 : 0);
+    const int tap = col / a.C;
+    const int c0 = col - tap * a.C;
+    tr[b] = tap / a.S;
+    ts[b] = tap - tr[b] * a.S;
+    tv[b] = col < Nw;
+    to[b] = (uint32_t)tr[b] * row_bytes + (uint32_t)ts[b] * pix_bytes +
+            (uint32_t)(c0 + (CGEN ? 0 : lc * 8)) * 2u;
   }
 
-  int64_t pstage = pbeg;  // first pixel of the next stage to issue
+  auto dma = [&](char* buf, int i) {
+    const int h = i % H, sub = i / H;
+    char* dst = buf + sub * 8192 + (4 * h + wave) * 1024;
+    if (sub < SA) {
+      const __amdgpu_buffer_rsrc_t rs_dy = __builtin_amdgcn_make_buffer_rsrc(
+          const_cast<h16*>(a.dy), (short)0, dy_bytes, 0x00020000);
+      const bool v = left[h] > 0 && av[sub];
+      wdma16(rs_dy, dst, v ? dyo[h] + (uint32_t)sub * 128u : OOB);
+    } else {
+      const __amdgpu_buffer_rsrc_t rs_x = __builtin_amdgcn_make_buffer_rsrc(
+          const_cast<h16*>(a.x), (short)0, x_bytes, 0x00020000);
+      const int b = sub - SA;
+      const bool v = left[h] > 0 && tv[b] && (unsigned)(ih0[h] + tr[b]) < (unsigned)a.H &&
+                     (unsigned)(iw0[h] + ts[b]) < (unsigned)a.W;
+      wdma16(rs_x, dst, v ? xo[h] + to[b] : OOB);
+    }
+  };
+  // the pixel rows 64 further
+  auto advance = [&]() {
+#pragma unroll
+    for (int h = 0; h < H; ++h) {
+      left[h] -= 64;
+      dyo[h] += 128u * (uint32_t)a.K;
+      int iw = iw0[h] + dq * a.sw;
+      const bool c1 = iw + a.pw >= a.Q * a.sw;
+      iw -= c1 ? a.Q * a.sw : 0;
+      int ih = ih0[h] + (dp + (c1 ? 1 : 0)) * a.sh;
+      const bool c2 = ih + a.ph >= a.P * a.sh;
+      ih -= c2 ? a.P * a.sh : 0;
+      xo[h] += (uint32_t)(dimg + (c2 ? 1 : 0)) * img_bytes +
+               (uint32_t)(ih - ih0[h]) * row_bytes + (uint32_t)(iw - iw0[h]) * pix_bytes;
+      ih0[h] = ih;
+      iw0[h] = iw;
+    }
+  };
   auto issue = [&](char* buf) {
-    const __amdgpu_buffer_rsrc_t rs_dy = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<h16*>(a.dy), (short)0, dy_bytes, 0x00020000);
-    const __amdgpu_buffer_rsrc_t rs_x = __builtin_amdgcn_make_buffer_rsrc(
-        const_cast<h16*>(a.x), (short)0, x_bytes, 0x00020000);
 #pragma unroll
-    for (int i = 0; i < IW; ++i) {
-      const int h = i & 1;
-      const int sub = i >> 1;
-      const int rb = 4 * h + wave;
-      char* dst = buf + sub * 8192 + rb * 1024;
-      const int64_t pix = pstage + prow[h];
-      const bool pv = pix < pend;
-      if (sub < SA) {
-        const int m = m0 + sub * 64;
-        const uint32_t off = (uint32_t)((pix * a.K + m + lc[h] * 8) * 2);
-        wdma16(rs_dy, dst, (pv && m < a.K) ? off : OOB);
-      } else if (CGEN) {
-        const int b = sub - SA;
-        const int ih = pp[h] * a.sh - a.ph + gr[h][b], iw = qq[h] * a.sw - a.pw + gt[h][b];
-        const bool v = pv && gc[h][b] >= 0 && (unsigned)ih < (unsigned)a.H &&
-                       (unsigned)iw < (unsigned)a.W;
-        const uint32_t off =
-            (uint32_t)(((((int64_t)img[h] * a.H + ih) * a.W + iw) * a.C + gc[h][b]) * 2);
-        wdma16(rs_x, dst, v ? off : OOB);
-      } else {
-        const int cb = n0 + (sub - SA) * 64;
-        const int tap = cb / a.C;
-        const int c0 = cb - tap * a.C;
-        const int r = tap / a.S, t = tap - r * a.S;
-        const int ih = pp[h] * a.sh - a.ph + r, iw = qq[h] * a.sw - a.pw + t;
-        const bool v = pv && cb < Nw && (unsigned)ih < (unsigned)a.H && (unsigned)iw < (unsigned)a.W;
-        const uint32_t off =
-            (uint32_t)(((((int64_t)img[h] * a.H + ih) * a.W + iw) * a.C + c0 + lc[h] * 8) * 2);
-        wdma16(rs_x, dst, v ? off : OOB);
-      }
-    }
-    // advance the two pixel rows by 64
-    pstage += 64;
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      qq[h] += dq;
-      const int c1 = qq[h] >= a.Q;
-      qq[h] -= c1 ? a.Q : 0;
-      pp[h] += dp + c1;
-      const int c2 = pp[h] >= a.P;
-      pp[h] -= c2 ? a.P : 0;
-      img[h] += dimg + c2;
-    }
+    for (int i = 0; i < IW; ++i) dma(buf, i);
+    advance();
   };
 
   const int wm = wave / WN, wn = wave % WN;
@@ -425,36 +279,56 @@ __global__ __launch_bounds__(256) void wgrad7_kernel(const WgradArgs a) {
 #pragma unroll
       for (int tn = 0; tn < TN; ++tn) lds_tie(fb[tn]);
     };
+    constexpr int PRE = SPREAD ? S - 1 : S;  // stages loaded ahead of the loop
 #pragma unroll
-    for (int s = 0; s < S; ++s) issue(lds + s * K::STAGE);
-    constexpr int ALLOW0 = IW * (S - 1);
+    for (int s = 0; s < PRE; ++s) issue(lds + s * K::STAGE);
+    constexpr int ALLOW0 = IW * (PRE - 1);
     constexpr int WAIT0 = (0x0 << 8) | (0x7 << 4) | (ALLOW0 & 0xF) | ((ALLOW0 >> 4) << 14);
     constexpr int ALLOW = IW * (S - 2);
     constexpr int WAIT = (0x0 << 8) | (0x7 << 4) | (ALLOW & 0xF) | ((ALLOW >> 4) << 14);
     __builtin_amdgcn_s_waitcnt(WAIT0);
     wbarrier();
     afetch(std::integral_constant<int, 0>(), 0u, af[0], bf[0]);
-    int rd = 0;
+    int rd = 0, wr = S - 1;
+    constexpr int P = (IW + 2) / 3;
+    auto part = [&](int q0, int q1) {  // SPREAD: some of stage kt+2's loads
+      if (SPREAD) {
+#pragma unroll
+        for (int i = q0; i < (q1 < IW ? q1 : IW); ++i) dma(lds + wr * K::STAGE, i);
+      }
+    };
+    auto fence = [&]() {
+      if (SPREAD) __builtin_amdgcn_sched_barrier(0);
+    };
     for (int kt = 0; kt < KT; ++kt) {
       const uint32_t cur = (uint32_t)(rd * K::STAGE);
       afetch(std::integral_constant<int, 1>(), cur, af[1], bf[1]);
+      part(0, P);
       ready(af[0], bf[0]);
       mma(af[0], bf[0]);
+      fence();
       afetch(std::integral_constant<int, 2>(), cur, af[0], bf[0]);
+      part(P, 2 * P);
       ready(af[1], bf[1]);
       mma(af[1], bf[1]);
+      fence();
       afetch(std::integral_constant<int, 3>(), cur, af[1], bf[1]);
+      part(2 * P, 3 * P);
       ready(af[0], bf[0]);
       mma(af[0], bf[0]);
+      if (SPREAD) advance();
+      fence();
       // every read of this stage is complete (lgkmcnt 0) and stage kt+1 has
       // landed (vmcnt) in every wave before the buffer is refilled
       __builtin_amdgcn_s_waitcnt(WAIT);
       wbarrier();
-      issue(lds + rd * K::STAGE);
+      if (!SPREAD) issue(lds + rd * K::STAGE);
       rd = rd + 1 == S ? 0 : rd + 1;
+      wr = wr + 1 == S ? 0 : wr + 1;
       afetch(std::integral_constant<int, 0>(), (uint32_t)(rd * K::STAGE), af[0], bf[0]);
       ready(af[1], bf[1]);
       mma(af[1], bf[1]);
+      fence();
     }
     __builtin_amdgcn_s_waitcnt(0);
   }
@@ -558,47 +432,63 @@ __global__ __launch_bounds__(256) void wgrad_reduce_vec_kernel(const float* __re
 // Tile configuration shared by the plan and the launch.
 struct WCfg {
   int BM, BN;
-  int S = 2;  // stages of the DMA ring (DMA-staged kernel)
+  int S = 2;   // stages of the DMA ring
+  int NW = 4;  // waves
 };
-// Larger tiles re-read less: a wider N tile reuses the dy tile over more
-// filter columns (three 3x3 taps at once for 64 output channels), a taller M
-// tile reuses the x tile over more output channels.  Each configuration has
-// at most one 8x8 load block per thread (BM + BN <= 256).
-inline WCfg wgrad_cfg(int K, int Nw) {
-  if (K >= 128 && Nw >= 128) return {128, 128};
-  if (K >= 128) return {128, 64};
-  if (Nw >= 192 && Nw % 192 == 0) return {64, 192};
-  if (Nw >= 128) return {64, 128};
-  return {64, 64};
-}
-// The DMA-staged kernel (channel counts multiples of 64) and its tiles.
-inline bool wgrad_dma(int K, int C) { return K % 64 == 0 && C % 8 == 0; }
-// (measured on the ResNet-50 shapes at batch 128: 128 x 128 tiles pay once
-// the pixel count is large enough to split them over the CUs, 128 x 64 below;
-// a third ring stage pays only for the single 64-column tile; 64 x 192 tiles
-// cover a 3x3 64-channel filter's 576 columns exactly, where 64 x 256 tiles
-// left a quarter of the third tile empty: conv2_x 60.4 -> 53.5 us)
-inline WCfg wgrad7_cfg(int K, int Nw, int64_t npix) {
-  if (K >= 128 && Nw >= 128 && npix >= 65536) return {128, 128};
-  if (K >= 128 && Nw <= 64) return {128, 64, 3};
-  if (K >= 128) return {128, 64};
+// From 65 output channels and 65 filter columns on: eight waves, one workgroup
+// per CU, the tile of the least
+//   rounds * k-steps of a split * area + splits * K * Nw * 1/8
+// among 128 x 128 and, where those come in a count that divides 256 badly,
+// 256 x 128 and 128 x 256 (splits = 256 / tiles; the units are one 128 x 128
+// k-step of 0.62 us at full load and the 8 bytes each partial sum moves).
+// Measured with the reduction, batch 128: 14x14 256 -> 256 3x3 55.5 -> 42.0 us
+// (four waves on 128 x 64, two workgroups per CU, 576 of them for 512 slots),
+// 28x28 128 -> 128 47.3 -> 42.3, 7x7 512 -> 512 53.4 -> 41.7 (256 x 128; 54 on
+// 128 x 128), 56x56 256 -> 512 1x1/2 49.8 -> 40.8, 14x14 256 -> 1024 28.6 ->
+// 26.1.
+// Fewer channels or columns: four waves (64 x 192 tiles cover a 3x3 64-channel
+// filter's 576 columns exactly, where 64 x 256 tiles left a quarter of the
+// third tile empty: conv2_x 60.4 -> 53.5 us).
+inline WCfg wgrad_choice(int K, int Nw, int64_t npix) {
+  if (K > 64 && Nw > 64) {
+    static constexpr int kShapes[3][2] = {{128, 128}, {256, 128}, {128, 256}};
+    WCfg best{128, 128, 3, 8};
+    double cost = 1e30;
+    for (const auto& t : kShapes) {
+      const int64_t tiles = (int64_t)ceil_div(K, t[0]) * ceil_div(Nw, t[1]);
+      const int64_t splits = tiles < 256 ? 256 / tiles : 1;
+      const int64_t steps = ceil_div64(ceil_div64(npix, BKP), splits);
+      const double c = (double)ceil_div64(tiles * splits, 256) * (double)steps * 0.62 *
+                           (t[0] * t[1] / 16384) +
+                       (double)splits * K * Nw * 8.0 / 4.0e6;
+      if (c < cost) {
+        cost = c;
+        best.BM = t[0];
+        best.BN = t[1];
+      }
+    }
+    return best;
+  }
+  if (K > 64) return {128, 64, 3};
   if (Nw % 192 == 0) return {64, 192};
   if (Nw >= 256) return {64, 256};
   if (Nw >= 128) return {64, 128};
   return {64, 64};
 }
-inline WCfg wgrad_choice(int K, int C, int Nw, int64_t npix) {
-  return wgrad_dma(K, C) ? wgrad7_cfg(K, Nw, npix) : wgrad_cfg(K, Nw);
-}
 
 template <bool CGEN>
 void launch_wgrad7(const WCfg& cfg, dim3 grid, hipStream_t st, const WgradArgs& a) {
-  if (cfg.BM == 128 && cfg.BN == 128)
-    hipLaunchKernelGGL((wgrad7_kernel<128, 128, 2, 2, 2, CGEN>), grid, dim3(256), 0, st, a);
-  else if (cfg.BM == 128 && cfg.S == 3)
+  if (cfg.NW == 8) {
+    if (cfg.BM == 256)
+      hipLaunchKernelGGL((wgrad7_kernel<256, 128, 4, 2, 3, CGEN>), grid, dim3(512), 0, st, a);
+    else if (cfg.BN == 256)
+      hipLaunchKernelGGL((wgrad7_kernel<128, 256, 2, 4, 3, CGEN>), grid, dim3(512), 0, st, a);
+    else
+      hipLaunchKernelGGL((wgrad7_kernel<128, 128, 4, 2, 3, CGEN>), grid, dim3(512), 0, st, a);
+    return;
+  }
+  if (cfg.BM == 128)
     hipLaunchKernelGGL((wgrad7_kernel<128, 64, 2, 2, 3, CGEN>), grid, dim3(256), 0, st, a);
-  else if (cfg.BM == 128)
-    hipLaunchKernelGGL((wgrad7_kernel<128, 64, 2, 2, 2, CGEN>), grid, dim3(256), 0, st, a);
   else if (cfg.BN == 256)
     hipLaunchKernelGGL((wgrad7_kernel<64, 256, 1, 4, 2, CGEN>), grid, dim3(256), 0, st, a);
   else if (cfg.BN == 192)
@@ -614,10 +504,15 @@ void launch_wgrad7(const WCfg& cfg, dim3 grid, hipStream_t st, const WgradArgs& 
 void wgrad_plan(int K, int Cp, int R, int S, int64_t npix, int target, int* splits,
                 int* pix_per_split) {
   const int Nw = R * S * Cp;
-  const WCfg cfg = wgrad_choice(K, Cp, Nw, npix);
+  const WCfg cfg = wgrad_choice(K, Nw, npix);
   const int64_t tiles = (int64_t)ceil_div(K, cfg.BM) * ceil_div(Nw, cfg.BN);
-  int64_t want = (target + tiles - 1) / tiles;  // about `target` workgroups
-  const int64_t max_splits = (npix + 2 * BKP - 1) / (2 * BKP);  // at least two k-steps each
+  // one workgroup per CU for the eight-wave kernel and for 1x1 filters, which
+  // are bound by reading x and dy (56x56 64 -> 256 at batch 128: 44 us with 256
+  // workgroups, 51 with 512); never more than the target, where a few more
+  // than the slots cost a round (14x14: 576 workgroups for 512 slots)
+  if ((cfg.NW == 8 || R * S == 1) && target > 256) target = 256;
+  int64_t want = target / tiles;
+  const int64_t max_splits = (npix + 4 * BKP - 1) / (4 * BKP);  // four k-steps each or more
   if (want > max_splits) want = max_splits;
   if (want < 1) want = 1;
   int64_t pps = (npix + want - 1) / want;
@@ -630,29 +525,14 @@ void wgrad_plan(int K, int Cp, int R, int S, int64_t npix, int target, int* spli
 
 hipError_t launch_wgrad_partial(const WgradArgs& a, hipStream_t st) {
   const int Nw = a.R * a.S * a.C;
-  const int64_t npix = (int64_t)a.N * a.P * a.Q;
-  const WCfg cfg = wgrad_choice(a.K, a.C, Nw, npix);
+  const WCfg cfg = wgrad_choice(a.K, Nw, (int64_t)a.N * a.P * a.Q);
   const int tiles = ceil_div(a.K, cfg.BM) * ceil_div(Nw, cfg.BN);
-  dim3 grid(tiles, a.splits);
-  if (wgrad_dma(a.K, a.C)) {
-    // channel counts that are multiples of 8 only (the 3-channel stem, padded)
-    // take per-lane filter taps
-    if (a.C % 64 != 0)
-      launch_wgrad7<true>(cfg, grid, st, a);
-    else
-      launch_wgrad7<false>(cfg, grid, st, a);
-    return hipGetLastError();
-  }
-  if (cfg.BM == 128 && cfg.BN == 128)
-    hipLaunchKernelGGL((wgrad_kernel<128, 128, 2, 2>), grid, dim3(256), 0, st, a);
-  else if (cfg.BM == 128)
-    hipLaunchKernelGGL((wgrad_kernel<128, 64, 2, 2>), grid, dim3(256), 0, st, a);
-  else if (cfg.BN == 192)
-    hipLaunchKernelGGL((wgrad_kernel<64, 192, 2, 2>), grid, dim3(256), 0, st, a);
-  else if (cfg.BN == 128)
-    hipLaunchKernelGGL((wgrad_kernel<64, 128, 2, 2>), grid, dim3(256), 0, st, a);
+  const dim3 grid(tiles, a.splits);
+  // channel counts that are not multiples of 64 take per-lane filter taps
+  if (a.C % 64 != 0)
+    launch_wgrad7<true>(cfg, grid, st, a);
   else
-    hipLaunchKernelGGL((wgrad_kernel<64, 64, 2, 2>), grid, dim3(256), 0, st, a);
+    launch_wgrad7<false>(cfg, grid, st, a);
   return hipGetLastError();
 }
 

@@ -176,9 +176,9 @@ hipError_t launch_wgrad_reduce(const float* partial, int splits, int K, int Kp, 
 // folded in place in groups first, so partial holds scratch afterwards).
 hipError_t launch_s2d3(const h16* src, h16* dst, int N, int H, int W, hipStream_t st);
 hipError_t launch_wgrad_reduce_s2d3(float* partial, int splits, int K, h16* dw, hipStream_t st);
-// Split-K plan of the weight gradient: about `target` workgroups (tiles x
-// splits; kWgradWorkgroups, two per CU, unless the caller asks for fewer),
-// each split at least two k-steps of pixels.
+// Split-K plan of the weight gradient: at most `target` workgroups (tiles x
+// splits; kWgradWorkgroups unless the caller asks for fewer, and 256 where one
+// per CU is the faster), each split at least four k-steps of pixels.
 constexpr int kWgradWorkgroups = 512;
 void wgrad_plan(int K, int Cp, int R, int S, int64_t npix, int target, int* splits,
                 int* pix_per_split);
