@@ -17,10 +17,12 @@
 // and the backward adds S3 = sum g*r to dgamma and sends gamma*g (rounded
 // once) to the shortcut.
 //
-// Bandwidth-bound.  The NHWC path (C a power-of-two multiple of 8, at most
-// 2048) gives each thread a fixed 8-channel chunk, so every access is a
-// 16-byte vector and per-channel coefficients are computed once per thread.
-// Other shapes and the NCHW layout use a generic per-element path.
+// Bandwidth-bound.  The NHWC path (C a multiple of 8, at most 2048) gives each
+// thread a fixed 8-channel chunk (the threads past the last whole row of
+// chunks of a workgroup idle where C/8 is not a power of two), so every access
+// is a 16-byte vector and per-channel coefficients are computed once per
+// thread.  NCHW takes chunks of 8 pixels of one channel.  Other channel counts
+// use a generic per-element path.
 // Reductions are float32 within a thread, combined in a fixed order within a
 // block and in float64 across blocks: the result does not depend on timing.
 
@@ -47,26 +49,29 @@ __device__ __forceinline__ int64_t geo_at(const Geo& g, int c, int64_t j) {
   const int64_t n = j / g.HW;
   return (n * g.C + c) * g.HW + (j - n * g.HW);
 }
-// channel of memory index i
-__device__ __forceinline__ int geo_chan(const Geo& g, int64_t i) {
-  return g.layout == 0 ? (int)(i % g.C) : (int)((i / g.HW) % g.C);
-}
 
 struct Plan {
+  // NHWC, 8-channel chunks: C % 8 == 0, C <= 2048 ([1, 100, 100, 1952] with a
+  // shortcut, forward and backward: 534 us on the per-element path, 106 here)
   bool vec;
-  int CV, RB, G;
+  bool whole;     // ... and the workgroup's threads divide into whole rows
+  bool nchw;
+  int CV, RB, TV, G;
   int64_t steps;  // vectorised reduces: row groups of RB rows of each block
-  int64_t rpb;    // generic reduces: elements per block
+  int64_t rpb;    // generic and NCHW reduces: elements or chunks per block
 };
 
 Plan make_plan(const BnArgs& a) {
   Plan p{};
   const int64_t M = (int64_t)a.N * a.H * a.W;
   const int CV = a.C / 8;
-  p.vec = a.layout == 0 && a.C % 8 == 0 && CV >= 1 && CV <= kT && (kT % CV) == 0;
+  p.vec = a.layout == 0 && a.C % 8 == 0 && CV >= 1 && CV <= kT;
+  p.nchw = a.layout != 0;
   if (p.vec) {
     p.CV = CV;
     p.RB = kT / CV;
+    p.TV = p.RB * CV;
+    p.whole = p.TV == kT;
     // about four vectors per thread, at most two blocks per CU: more blocks
     // only add partial sums (on the conv2_x block's last BN backward 965
     // blocks took 27.4 us, 502 took 26.0)
@@ -75,6 +80,14 @@ Plan make_plan(const BnArgs& a) {
     if (G < 1) G = 1;
     p.steps = (M + G * p.RB - 1) / (G * p.RB);
     p.G = (int)((M + p.steps * p.RB - 1) / (p.steps * p.RB));
+  } else if (p.nchw) {
+    // chunks of 8 pixels of one image row of the channel; about four per thread
+    const int64_t items = (int64_t)a.N * (((int64_t)a.H * a.W + 7) / 8);
+    int64_t G = (items + 4 * kT - 1) / (4 * kT);
+    if (G > 64) G = 64;
+    if (G < 1) G = 1;
+    p.rpb = (items + G - 1) / G;
+    p.G = (int)((items + p.rpb - 1) / p.rpb);
   } else {
     int64_t G = (M + 8 * kT - 1) / (8 * kT);
     if (G > 64) G = 64;
@@ -101,8 +114,9 @@ __device__ __forceinline__ bool relu_mask(bool relu, bool has_y, h16 y, float x,
 // Thread t holds sums[v][8] (v < NS) for the 8 channels of chunk j = t % CV.
 // Lanes of one wave that hold the same chunk are combined by a butterfly
 // over the lane bits at or above log2(CV); the waves' totals (or, for
-// CV > 64, the threads' own values) are then summed in a fixed order from
-// LDS and written either block-major, out[(block * NS + v) * C + c] (bm:
+// other CV, the threads' own values) are then summed in a fixed order from
+// LDS (so also where CV is not a power of two; then the threads from RB * CV
+// on hold nothing) and written either block-major, out[(block * NS + v) * C + c] (bm:
 // each block writes its sums as one contiguous run; from 256 channels on),
 // or channel-major, out[(v * C + c) * G + block] (fewer channels: the
 // finalize then spreads over one block per channel).  red: [8 * NS][kT].
@@ -112,7 +126,7 @@ __device__ __forceinline__ void block_reduce_vec(float (&sums)[NS][8], float* re
   const int t = threadIdx.x;
   const int lane = t & 63;
   int groups;
-  if (CV <= 64) {
+  if (CV <= 64 && (CV & (CV - 1)) == 0) {
     for (int off = CV; off < 64; off <<= 1) {
 #pragma unroll
       for (int v = 0; v < NS; ++v)
@@ -168,6 +182,7 @@ __global__ __launch_bounds__(kT) void bn_fwd_reduce_vec(const h16* __restrict__ 
   // four rows in flight per thread, the sums row by row; the step count is
   // the launch's, and a row past the last is loaded clamped (in bounds) and
   // adds exact zeros, so no load waits behind a condition
+  const bool act = t < RB * CV;
   const int64_t rt = (int64_t)blockIdx.x * RB + t / CV;
   const int64_t RS = (int64_t)RB * gridDim.x;
   for (int64_t i = 0; i < nsteps; i += 4) {
@@ -180,7 +195,7 @@ __global__ __launch_bounds__(kT) void bn_fwd_reduce_vec(const h16* __restrict__ 
     __builtin_amdgcn_sched_barrier(0);  // every load issued before the first use
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const bool ok = rt + (i + u) * RS < g.M;
+      const bool ok = act && rt + (i + u) * RS < g.M;
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const float d = ok ? to_f32(v[u].h[e]) - sh[e] : 0.0f;
@@ -519,7 +534,8 @@ __global__ __launch_bounds__(64) void bn_band_combine(const float* __restrict__ 
 //   byte per 16-byte vector of y, bit e = [y element e > 0]).
 constexpr int kSwap = 1, kRelu = 2, kMaskY = 4, kLoadR = 8, kDres = 16, kMaskB = 32, kKeepF = 64;
 
-// Each block takes runs of kApplyU * kT consecutive 16-byte vectors; a thread
+// Each block takes runs of kApplyU * TV consecutive 16-byte vectors (TV: the
+// threads that make whole rows of C/8 chunks, kT where C/8 is a power of two); a thread
 // loads its kApplyU vectors (and residual vectors) before it stores any, so
 // several loads per thread are in flight.  The run loop is the block's; a
 // vector past the end is loaded clamped (in bounds) and not stored.  y may
@@ -544,24 +560,24 @@ template <int MODE>
 __global__ __launch_bounds__(kT) void bn_fwd_apply_vec(const h16* x, const h16* __restrict__ gamma,
                                                        const h16* __restrict__ beta, const h16* res,
                                                        h16* y, const float* __restrict__ stats,
-                                                       Geo g, int CV, float s,
+                                                       Geo g, int CV, int TV, float s,
                                                        uint8_t* __restrict__ mout) {
   constexpr bool SWAP = MODE & kSwap, RELU = MODE & kRelu, HAS_R = MODE & kLoadR,
                  KEEP = MODE & kKeepF;
   const int t = threadIdx.x;
-  const int j = t % CV;  // run starts and kT are multiples of CV
+  const int j = t % CV;  // run starts and TV are multiples of CV
   FwdCoef k[8];
 #pragma unroll
   for (int e = 0; e < 8; ++e) k[e] = fwd_coef(stats, gamma, beta, g.C, j * 8 + e, s);
   const int64_t nvec = g.M * CV;
-  constexpr int64_t RUN = (int64_t)kApplyU * kT;
+  const int64_t RUN = (int64_t)kApplyU * TV;
   const int64_t nruns = (nvec + RUN - 1) / RUN;
   for (int64_t r = nruns - 1 - blockIdx.x; r >= 0; r -= gridDim.x) {
     const int64_t run = r * RUN;
     V8 xv[kApplyU], rv[kApplyU];
 #pragma unroll
     for (int u = 0; u < kApplyU; ++u) {
-      const int64_t v = run + t + u * kT;
+      const int64_t v = run + t + u * TV;
       const int64_t vc = v < nvec ? v : nvec - 1;
       xv[u] = load16_last(x + vc * 8);
       if (HAS_R) rv[u] = load16(res + vc * 8);
@@ -569,7 +585,7 @@ __global__ __launch_bounds__(kT) void bn_fwd_apply_vec(const h16* x, const h16* 
     __builtin_amdgcn_sched_barrier(0);  // every load issued before the first use
 #pragma unroll
     for (int u = 0; u < kApplyU; ++u) {
-      const int64_t v = run + t + u * kT;
+      const int64_t v = run + t + u * TV;
       V8 out;
       uint32_t bits = 0;
 #pragma unroll
@@ -578,7 +594,7 @@ __global__ __launch_bounds__(kT) void bn_fwd_apply_vec(const h16* x, const h16* 
                                     HAS_R ? to_f32(rv[u].h[e]) : 0.0f, RELU, SWAP));
         if (KEEP) bits |= (uint32_t)(to_f32(out.h[e]) > 0.0f) << e;
       }
-      if (v < nvec) {
+      if (t < TV && v < nvec) {
         store16(y + v * 8, out);
         if (KEEP) mout[v] = (uint8_t)bits;
       }
@@ -593,7 +609,7 @@ __global__ __launch_bounds__(kT) void bn_fwd_apply_gen(const h16* x, const h16* 
   const int64_t total = g.M * g.C;
   for (int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x; i < total;
        i += (int64_t)gridDim.x * kT) {
-    const int c = geo_chan(g, i);
+    const int c = (int)(i % g.C);
     const FwdCoef k = fwd_coef(stats, gamma, beta, g.C, c, s);
     y[i] = to_h16(fwd_value(to_f32(x[i]), k, res != nullptr, res ? to_f32(res[i]) : 0.0f,
                             relu != 0, g.swap != 0));
@@ -639,6 +655,7 @@ __global__ __launch_bounds__(kT) void bn_bwd_reduce_vec(const h16* __restrict__ 
     V8 x, d, y, r;
     uint32_t mb;
   };
+  const bool act = t < RB * CV;
   const int64_t rt = (int64_t)blockIdx.x * RB + t / CV;
   const int64_t RS = (int64_t)RB * gridDim.x;
   auto load_row = [&](Row& b, int64_t i) {
@@ -652,7 +669,7 @@ __global__ __launch_bounds__(kT) void bn_bwd_reduce_vec(const h16* __restrict__ 
     if (MASK_B) b.mb = mbits[row * CV + j];
   };
   auto sum_row = [&](const Row& b, int64_t i) {
-    const bool ok = rt + i * RS < g.M;
+    const bool ok = act && rt + i * RS < g.M;
     uint32_t bits = 0;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
@@ -774,7 +791,7 @@ __global__ __launch_bounds__(kT) void bn_bwd_apply_vec(const h16* x, const h16* 
                                                        const h16* __restrict__ beta, const h16* res,
                                                        const float* __restrict__ stats,
                                                        const float* __restrict__ coef, Geo g,
-                                                       int CV, float s,
+                                                       int CV, int TV, float s,
                                                        const uint8_t* __restrict__ mbits, h16* dx,
                                                        h16* dres) {
   constexpr bool SWAP = MODE & kSwap, RELU = MODE & kRelu, MASK_Y = MODE & kMaskY,
@@ -784,7 +801,7 @@ __global__ __launch_bounds__(kT) void bn_bwd_apply_vec(const h16* x, const h16* 
   // shortcut's 16
   constexpr bool NEED_R = ((MODE & kLoadR) && RELU && !MASK_Y) || (MODE & kMaskB);
   const int t = threadIdx.x;
-  const int j = t % CV;  // run starts and kT are multiples of CV
+  const int j = t % CV;  // run starts and TV are multiples of CV
   FwdCoef k[8];
   float A[8], B[8], D[8], gam[8];
 #pragma unroll
@@ -798,7 +815,7 @@ __global__ __launch_bounds__(kT) void bn_bwd_apply_vec(const h16* x, const h16* 
   }
   const int64_t nvec = g.M * CV;
   constexpr int U = kApplyU / 2;  // vectors per thread and run: 2 to 4 loads each
-  constexpr int64_t RUN = (int64_t)U * kT;
+  const int64_t RUN = (int64_t)U * TV;
   const int64_t nruns = (nvec + RUN - 1) / RUN;
   for (int64_t r = nruns - 1 - blockIdx.x; r >= 0; r -= gridDim.x) {
     const int64_t run = r * RUN;
@@ -806,7 +823,7 @@ __global__ __launch_bounds__(kT) void bn_bwd_apply_vec(const h16* x, const h16* 
     uint32_t mb[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int64_t v = run + t + u * kT;
+      const int64_t v = run + t + u * TV;
       const int64_t vc = v < nvec ? v : nvec - 1;
       xv[u] = load16_last(x + vc * 8);
       dv[u] = load16_last(dy + vc * 8);
@@ -816,7 +833,7 @@ __global__ __launch_bounds__(kT) void bn_bwd_apply_vec(const h16* x, const h16* 
     __builtin_amdgcn_sched_barrier(0);  // every load issued before the first use
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int64_t v = run + t + u * kT;
+      const int64_t v = run + t + u * TV;
       V8 o, od;
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
@@ -831,7 +848,7 @@ __global__ __launch_bounds__(kT) void bn_bwd_apply_vec(const h16* x, const h16* 
         else
           od.s[e] = m ? dv[u].s[e] : (uint16_t)0;
       }
-      if (v < nvec) {
+      if (t < TV && v < nvec) {
         store16(dx + v * 8, o);
         if (DRES) store16_far(dres + v * 8, od);
       }
@@ -850,7 +867,7 @@ __global__ __launch_bounds__(kT) void bn_bwd_apply_gen(const h16* x, const h16* 
   const bool has_y = y != nullptr, has_r = res != nullptr && !has_y && relu;
   for (int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x; i < total;
        i += (int64_t)gridDim.x * kT) {
-    const int c = geo_chan(g, i);
+    const int c = (int)(i % g.C);
     const FwdCoef k = fwd_coef(stats, gamma, beta, g.C, c, s);
     const float xf = to_f32(x[i]);
     const h16 dyv = dy[i];
@@ -859,6 +876,178 @@ __global__ __launch_bounds__(kT) void bn_bwd_apply_gen(const h16* x, const h16* 
     const float gg = m ? s * to_f32(dyv) : 0.0f;
     dx[i] = to_h16(coef[c] * (gg - __builtin_fmaf(xf - k.mean, coef[2 * g.C + c], coef[g.C + c])));
     if (dres) dres[i] = swap ? to_h16(to_f32(gamma[c]) * gg) : (m ? dyv : (h16)0.0f);
+  }
+}
+
+// ---- NCHW -------------------------------------------------------------------------
+// A channel's elements are N runs of HW values.  Chunks of 8 consecutive
+// values of one run (the run's last may be partial; runs start at any 2-byte
+// alignment) are read and written 16 bytes at a time.  The reduces take one
+// channel and a range of its chunks per workgroup, four chunks per thread in
+// flight; the applies one chunk per thread and step.  ([32, 256, 28, 28],
+// forward and backward: 66.6 us one element per thread, 33.5 now, the
+// six launches a third of it.)
+__device__ __forceinline__ V8 chunk_load(const h16* p, int left) {
+  V8 v;
+  if (left >= 8) {
+    __builtin_memcpy(&v, p, 16);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v.h[e] = e < left ? p[e] : (h16)0.0f;
+  }
+  return v;
+}
+__device__ __forceinline__ void chunk_store(h16* p, int left, const V8& v) {
+  if (left >= 8) {
+    __builtin_memcpy(p, &v, 16);
+  } else {
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      if (e < left) p[e] = v.h[e];
+  }
+}
+
+__global__ __launch_bounds__(kT) void bn_fwd_reduce_nchw(const h16* __restrict__ x, Geo g, int PC,
+                                                         int items, int per, float* ws) {
+  __shared__ float red[2 * kT];
+  const int c = blockIdx.y;
+  const int i0 = blockIdx.x * per;
+  const int i1 = i0 + per < items ? i0 + per : items;
+  const float sh = to_f32(x[geo_at(g, c, 0)]);
+  float v[2] = {0.0f, 0.0f};
+  constexpr int U = 4;
+  for (int i = i0 + (int)threadIdx.x; i < i1; i += U * kT) {
+    V8 xv[U];
+    int left[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = i + u * kT < i1 ? i + u * kT : i;
+      const int n = k / PC, q = k - n * PC;
+      left[u] = i + u * kT < i1 ? g.HW - q * 8 : 0;
+      xv[u] = chunk_load(x + ((int64_t)n * g.C + c) * g.HW + q * 8, g.HW - q * 8);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float d = e < left[u] ? to_f32(xv[u].h[e]) - sh : 0.0f;
+        v[0] += d;
+        v[1] = __builtin_fmaf(d, d, v[1]);
+      }
+  }
+  block_reduce_1<2>(v, red);
+  if (threadIdx.x == 0) {
+    ws[(int64_t)c * gridDim.x + blockIdx.x] = v[0];
+    ws[((int64_t)g.C + c) * gridDim.x + blockIdx.x] = v[1];
+  }
+}
+
+template <bool HAS_R>
+__global__ __launch_bounds__(kT) void bn_fwd_apply_nchw(const h16* x,
+                                                        const h16* __restrict__ gamma,
+                                                        const h16* __restrict__ beta,
+                                                        const h16* res, h16* y,
+                                                        const float* __restrict__ stats, Geo g,
+                                                        int PC, int items, float s, int relu) {
+  for (int i = blockIdx.x * kT + threadIdx.x; i < items; i += gridDim.x * kT) {
+    const int row = i / PC, q = i - row * PC;
+    const int c = row % g.C, left = g.HW - q * 8;
+    const int64_t at = (int64_t)row * g.HW + q * 8;
+    const V8 xv = chunk_load(x + at, left);
+    V8 rv = zero8();
+    if (HAS_R) rv = chunk_load(res + at, left);
+    const FwdCoef k = fwd_coef(stats, gamma, beta, g.C, c, s);
+    V8 o;
+#pragma unroll
+    for (int e = 0; e < 8; ++e)
+      o.h[e] = to_h16(fwd_value(to_f32(xv.h[e]), k, HAS_R, HAS_R ? to_f32(rv.h[e]) : 0.0f,
+                                relu != 0, g.swap != 0));
+    chunk_store(y + at, left, o);
+  }
+}
+
+// LR: the shortcut is read (the BN swap, or the mask recomputed from it); HY:
+// the mask comes from the stored output
+template <bool LR, bool HY>
+__global__ __launch_bounds__(kT) void bn_bwd_reduce_nchw(
+    const h16* __restrict__ x, const h16* __restrict__ y, const h16* __restrict__ dy,
+    const h16* __restrict__ gamma, const h16* __restrict__ beta, const h16* __restrict__ res,
+    const float* __restrict__ stats, Geo g, int PC, int items, int per, float s, int relu,
+    float* ws) {
+  __shared__ float red[3 * kT];
+  const int c = blockIdx.y;
+  const int i0 = blockIdx.x * per;
+  const int i1 = i0 + per < items ? i0 + per : items;
+  const FwdCoef k = fwd_coef(stats, gamma, beta, g.C, c, s);
+  const bool swap = g.swap != 0;
+  float v[3] = {0.0f, 0.0f, 0.0f};
+  constexpr int U = 2;
+  for (int i = i0 + (int)threadIdx.x; i < i1; i += U * kT) {
+    V8 xv[U], dv[U], yv[U], rv[U];
+    int left[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int m = i + u * kT < i1 ? i + u * kT : i;
+      const int n = m / PC, q = m - n * PC;
+      const int l = g.HW - q * 8;
+      const int64_t at = ((int64_t)n * g.C + c) * g.HW + q * 8;
+      left[u] = i + u * kT < i1 ? l : 0;
+      xv[u] = chunk_load(x + at, l);
+      dv[u] = chunk_load(dy + at, l);
+      if (HY) yv[u] = chunk_load(y + at, l);
+      if (LR) rv[u] = chunk_load(res + at, l);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float xf = to_f32(xv[u].h[e]), rf = LR ? to_f32(rv[u].h[e]) : 0.0f;
+        const bool m = relu_mask(relu != 0, HY, HY ? yv[u].h[e] : (h16)0.0f, xf, k, LR, rf, swap);
+        const bool ok = e < left[u];
+        const float gg = ok && m ? s * to_f32(dv[u].h[e]) : 0.0f;
+        v[0] += gg;
+        v[1] = __builtin_fmaf(gg, ok ? xf - k.mean : 0.0f, v[1]);
+        v[2] = __builtin_fmaf(gg, ok ? rf : 0.0f, v[2]);
+      }
+  }
+  block_reduce_1<3>(v, red);
+  if (threadIdx.x == 0) {
+    const int64_t G = gridDim.x;
+    for (int q = 0; q < (swap ? 3 : 2); ++q) ws[((int64_t)q * g.C + c) * G + blockIdx.x] = v[q];
+  }
+}
+
+template <bool LR, bool HY>
+__global__ __launch_bounds__(kT) void bn_bwd_apply_nchw(
+    const h16* x, const h16* y, const h16* dy, const h16* __restrict__ gamma,
+    const h16* __restrict__ beta, const h16* res, const float* __restrict__ stats,
+    const float* __restrict__ coef, Geo g, int PC, int items, float s, int relu, h16* dx,
+    h16* dres) {
+  const bool swap = g.swap != 0;
+  for (int i = blockIdx.x * kT + threadIdx.x; i < items; i += gridDim.x * kT) {
+    const int row = i / PC, q = i - row * PC;
+    const int c = row % g.C, left = g.HW - q * 8;
+    const int64_t at = (int64_t)row * g.HW + q * 8;
+    const V8 xv = chunk_load(x + at, left), dv = chunk_load(dy + at, left);
+    V8 yv = zero8(), rv = zero8();
+    if (HY) yv = chunk_load(y + at, left);
+    if (LR) rv = chunk_load(res + at, left);
+    const FwdCoef k = fwd_coef(stats, gamma, beta, g.C, c, s);
+    const float A = coef[c], B = coef[g.C + c], D = coef[2 * g.C + c], gam = to_f32(gamma[c]);
+    V8 o, od;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const float xf = to_f32(xv.h[e]);
+      const bool m = relu_mask(relu != 0, HY, yv.h[e], xf, k, LR, LR ? to_f32(rv.h[e]) : 0.0f, swap);
+      const float gg = m ? s * to_f32(dv.h[e]) : 0.0f;
+      o.h[e] = to_h16(A * (gg - __builtin_fmaf(xf - k.mean, D, B)));
+      if (swap)
+        od.h[e] = to_h16(gam * gg);
+      else
+        od.s[e] = m ? dv.s[e] : (uint16_t)0;
+    }
+    chunk_store(dx + at, left, o);
+    if (dres) chunk_store(dres + at, left, od);
   }
 }
 
@@ -980,7 +1169,7 @@ hipError_t launch_fwd_apply_vec(int mode, const Plan& p, const Geo& g, const h16
 #define FP16K_CASE(m)                                                                          \
   case m:                                                                                      \
     hipLaunchKernelGGL(bn_fwd_apply_vec<m>, grid, dim3(kT), 0, st, x, gamma, beta, res, y,     \
-                       stats, g, p.CV, s, mout);                                                \
+                       stats, g, p.CV, p.TV, s, mout);                                          \
     break;
     FP16K_BN_FWD_MODES(FP16K_CASE)
 #undef FP16K_CASE
@@ -1024,17 +1213,24 @@ size_t bn_ws_bytes(const BnArgs& a) {
 }
 
 // Bytes of a kept ReLU mask (one byte per 8 channels of each pixel), or 0
-// where the vectorised kernels do not run or there is no ReLU.
+// where it is not offered (C/8 not a power of two up to 256) or there is no
+// ReLU.
 size_t bn_keep_mask_bytes(const BnArgs& a) {
   const Plan p = make_plan(a);
-  return p.vec && a.relu ? (size_t)((int64_t)a.N * a.H * a.W * p.CV) : 0;
+  return p.vec && p.whole && a.relu ? (size_t)((int64_t)a.N * a.H * a.W * p.CV) : 0;
 }
+
+// Chunks of 8 of an NCHW image row of one channel.
+static int nchw_chunks(const BnArgs& a) { return (a.H * a.W + 7) / 8; }
 
 // The batch statistics of x into stats (the partial sums in ws).
 static void bn_fwd_stats(const BnArgs& a, const Plan& p, const Geo& g, const h16* x, float* stats,
                          void* ws, hipStream_t st) {
   float* part = reinterpret_cast<float*>(ws);
-  if (p.vec)
+  if (p.nchw)
+    hipLaunchKernelGGL(bn_fwd_reduce_nchw, dim3(p.G, a.C), dim3(kT), 0, st, x, g, nchw_chunks(a),
+                       a.N * nchw_chunks(a), (int)p.rpb, part);
+  else if (p.vec)
     hipLaunchKernelGGL(bn_fwd_reduce_vec, dim3(p.G), dim3(kT), 0, st, x, g, p.CV, p.RB, p.steps,
                        part);
   else
@@ -1052,7 +1248,16 @@ hipError_t launch_bn_fwd(const BnArgs& a, const h16* x, const h16* gamma, const 
   const Plan p = make_plan(a);
   const Geo g = make_geo(a);
   if (!use_stats) bn_fwd_stats(a, p, g, x, stats, ws, st);
-  if (p.vec) {
+  if (p.nchw) {
+    const int PC = nchw_chunks(a), items = a.N * a.C * PC;
+    const dim3 grid(apply_grid(items, 1));
+    if (res)
+      hipLaunchKernelGGL(bn_fwd_apply_nchw<true>, grid, dim3(kT), 0, st, x, gamma, beta, res, y,
+                         stats, g, PC, items, a.post_scale, a.relu);
+    else
+      hipLaunchKernelGGL(bn_fwd_apply_nchw<false>, grid, dim3(kT), 0, st, x, gamma, beta, res, y,
+                         stats, g, PC, items, a.post_scale, a.relu);
+  } else if (p.vec) {
     const hipError_t e =
         launch_fwd_apply_vec(fwd_mode(a, res, mout != nullptr), p, g, x, gamma, beta, res, y, stats,
                              a.post_scale, mout, st);
@@ -1065,7 +1270,7 @@ hipError_t launch_bn_fwd(const BnArgs& a, const h16* x, const h16* gamma, const 
 }
 
 bool bn_maxpool_ok(const BnArgs& a, const PoolArgs& pa) {
-  return make_plan(a).vec && a.relu && !a.swap && pa.layout == 0 && pa.N == a.N &&
+  return make_plan(a).whole && a.relu && !a.swap && pa.layout == 0 && pa.N == a.N &&
          pa.C == a.C && pa.H == a.H && pa.W == a.W && pa.R == 3 && pa.S == 3;
 }
 
@@ -1134,9 +1339,30 @@ hipError_t launch_bn_bwd(const BnArgs& a, const h16* x, const h16* y, const h16*
   // reduce fills when it recomputes the mask from the shortcut
   uint8_t* mbits = mask ? const_cast<uint8_t*>(mask)
                         : reinterpret_cast<uint8_t*>(ws) + partial_bytes(p, a.C) + coef_bytes(a.C);
-  if (mask && (!p.vec || a.swap || !a.relu)) return hipErrorInvalidValue;
+  if (mask && (!p.whole || a.swap || !a.relu)) return hipErrorInvalidValue;
   const int mode = bwd_mode(a, y, res, dres, mask != nullptr);
-  if (p.vec) {
+  // NCHW: which of the stored output and the shortcut are read
+  const bool hy = a.relu && y, lr = a.swap || (a.relu && !y && res);
+  const int PC = nchw_chunks(a);
+#define FP16K_NCHW(kernel, grid, ...)                                                           \
+  do {                                                                                          \
+    if (lr && hy)                                                                               \
+      hipLaunchKernelGGL((kernel<true, true>), grid, dim3(kT), 0, st, x, y, dy, gamma, beta,    \
+                         res, stats, __VA_ARGS__);                                              \
+    else if (lr)                                                                                \
+      hipLaunchKernelGGL((kernel<true, false>), grid, dim3(kT), 0, st, x, y, dy, gamma, beta,   \
+                         res, stats, __VA_ARGS__);                                              \
+    else if (hy)                                                                                \
+      hipLaunchKernelGGL((kernel<false, true>), grid, dim3(kT), 0, st, x, y, dy, gamma, beta,   \
+                         res, stats, __VA_ARGS__);                                              \
+    else                                                                                        \
+      hipLaunchKernelGGL((kernel<false, false>), grid, dim3(kT), 0, st, x, y, dy, gamma, beta,  \
+                         res, stats, __VA_ARGS__);                                              \
+  } while (0)
+  if (p.nchw) {
+    FP16K_NCHW(bn_bwd_reduce_nchw, dim3(p.G, a.C), g, PC, a.N * PC, (int)p.rpb, a.post_scale,
+               a.relu, part);
+  } else if (p.vec) {
     switch (mode & ~kDres) {
 #define FP16K_CASE(m)                                                                          \
   case m:                                                                                      \
@@ -1161,13 +1387,18 @@ hipError_t launch_bn_bwd(const BnArgs& a, const h16* x, const h16* y, const h16*
   else
     hipLaunchKernelGGL(bn_bwd_finalize_bm<2>, dim3((a.C + 63) / 64), dim3(64 * kFinW), 0, st, g,
                        p.G, part, gamma, stats, dgamma, dbeta, coef);
-  if (p.vec) {
+  if (p.nchw) {
+    const int items = a.N * a.C * PC;
+    FP16K_NCHW(bn_bwd_apply_nchw, dim3(apply_grid(items, 1)), coef, g, PC, items, a.post_scale,
+               a.relu, dx, dres);
+#undef FP16K_NCHW
+  } else if (p.vec) {
     const dim3 grid(apply_grid(g.M * p.CV / (kApplyU / 2), p.CV));
     switch (mode) {
 #define FP16K_CASE(m)                                                                          \
   case m:                                                                                      \
     hipLaunchKernelGGL(bn_bwd_apply_vec<m>, grid, dim3(kT), 0, st, x, y, dy, gamma, beta, res, \
-                       stats, coef, g, p.CV, a.post_scale, mbits, dx, dres);                    \
+                       stats, coef, g, p.CV, p.TV, a.post_scale, mbits, dx, dres);              \
     break;
       FP16K_BN_BWD_APPLY_MODES(FP16K_CASE)
 #undef FP16K_CASE

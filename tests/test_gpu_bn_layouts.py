@@ -1,0 +1,95 @@
+"""BN at channel counts whose 8-channel chunks are not a power of two (NHWC) and
+in NCHW at image sizes around the 8-value chunks: the forward bit for bit the
+same in both layouts given the statistics, statistics and backward against
+float64 in plain torch.
+
+Bounds: statistics 2e-6 of the spread; dgamma and dbeta one rounding plus
+M * 2^-24 of the sum of magnitudes; dx one rounding plus 1e-5 of the magnitudes
+its float32 sequence adds."""
+
+import pytest
+import torch
+
+import paper_1911_07384_amd as F
+from gpu_util import require_gpu
+
+pytestmark = pytest.mark.gpu
+
+EPS, SCALE = 1e-5, 0.25
+# (n, c, h, w)
+SHAPES = [(2, 24, 5, 3), (3, 160, 9, 7), (2, 72, 14, 14), (1, 1000, 3, 5), (5, 136, 1, 1),
+          (2, 2040, 2, 2), (4, 40, 33, 31), (3, 16, 7, 7), (2, 5, 4, 2), (1, 7, 61, 67),
+          (40, 8, 8, 16), (3, 264, 28, 28)]
+
+
+@pytest.mark.parametrize("form", ["plain", "residual", "stored", "norelu", "swap"])
+@pytest.mark.parametrize("shape", SHAPES, ids=["x".join(map(str, s)) for s in SHAPES])
+def test_layouts(shape, form):
+    require_gpu()
+    n, c, h, w = shape
+    M = n * h * w
+    relu, swap = form != "norelu", form == "swap"
+    g = torch.Generator(device="cuda")
+    g.manual_seed(31)
+
+    def rnd(*s, std=1.0, mean=0.0):
+        return (torch.randn(s, generator=g, device="cuda") * std + mean).half()
+
+    x, dy = rnd(n, h, w, c, mean=0.2), rnd(n, h, w, c, std=1e-2)
+    gamma, beta = rnd(c, std=0.3, mean=1.0), rnd(c, std=0.3)
+    res = rnd(n, h, w, c) if form in ("residual", "stored", "swap") else None
+
+    def run(layout):
+        def put(t):
+            return t if t is None or layout == "NHWC" else t.permute(0, 3, 1, 2).contiguous()
+
+        def back(t):
+            return t if layout == "NHWC" else t.permute(0, 2, 3, 1).contiguous()
+
+        X, D, R = put(x), put(dy), put(res)
+        d = F.bn_desc(n, c, h, w, layout, EPS, SCALE, relu, swap=swap)
+        ws = F.workspace(F.fp16_bn_workspace_bytes(d))
+        st = torch.empty(2 * c, dtype=torch.float32, device="cuda")
+        y = torch.full_like(X, float("nan"))
+        F.fp16_bn_relu(d, X, gamma, beta, R, y, st, ws)
+        fixed = torch.cat([x.float().view(-1, c).mean(0), 1.0 / x.float().view(-1, c).std(0, unbiased=False)
+                           if M > 1 else torch.ones(c, device="cuda")])
+        du = F.bn_desc(n, c, h, w, layout, EPS, SCALE, relu, use_stats=True, swap=swap)
+        yu = X.clone()  # in place
+        F.fp16_bn_relu(du, yu, gamma, beta, R, yu, fixed, ws)
+        dx, dres = torch.full_like(X, float("nan")), torch.full_like(X, float("nan"))
+        dg, db = torch.empty_like(gamma), torch.empty_like(beta)
+        F.fp16_bn_relu_bwd(du, X, yu if form == "stored" else None, D, gamma, beta, R, fixed, dx, dg,
+                           db, dres if res is not None else None, ws)
+        return st, back(yu), fixed, back(dx), dg, db, back(dres)
+
+    a, b = run("NHWC"), run("NCHW")
+    x64 = x.double().view(M, c)
+    mean, var = x64.mean(0), x64.var(0, unbiased=False)
+    sd = (var + EPS).sqrt()
+    for st, yu, fixed, dx, dg, db, dres in (a, b):
+        assert ((st[:c].double() - mean).abs() / sd).max().item() < 2e-6
+        assert ((st[c:].double() * sd) - 1).abs().max().item() < 4e-6
+        m, r = fixed[:c].double(), fixed[c:].double()
+        mask = (yu.view(M, c) > 0) if relu else torch.ones((M, c), dtype=torch.bool, device="cuda")
+        G = SCALE * dy.double().view(M, c) * mask
+        xh = (x64 - m) * r
+        s1, s2, mag = G.sum(0), (G * xh).sum(0), (G.abs() * (1 + xh.abs())).sum(0)
+        s3 = 0.0
+        if swap:
+            s3 = (G * res.double().view(M, c)).sum(0)
+            mag = mag + (G * res.double().view(M, c)).abs().sum(0)
+        tol = (M + 4) * 2.0 ** -24 * mag + 2.0 ** -25
+        assert ((db.double() - s1).abs() <= s1.abs() * 2.0 ** -11 + tol).all()
+        assert ((dg.double() - (s2 + s3)).abs() <= (s2 + s3).abs() * 2.0 ** -11 + tol).all()
+        A = gamma.double() * r
+        ref = A * (G - s1 / M - xh * (s2 / M))
+        parts = A.abs() * (G.abs() + (s1 / M).abs() + (xh * (s2 / M)).abs() + mag / M)
+        err = (dx.double().view(M, c) - ref).abs()
+        assert (err <= ref.abs() * 2.0 ** -11 + 1e-5 * parts + 2.0 ** -25).all()
+        if swap:
+            want = gamma.double() * G
+            assert ((dres.double().view(M, c) - want).abs() <= want.abs() * 2.0 ** -10 + 2.0 ** -24).all()
+        elif res is not None:
+            assert torch.equal(dres.view(M, c), torch.where(mask, dy.view(M, c), torch.zeros_like(x.view(M, c))))
+    assert torch.equal(a[1], b[1])
