@@ -2095,14 +2095,19 @@ enum class IgemmKind { kWide, kDirect, kDma, kPointwise, k3x3 };
 //    128 of 56x56 45.7 against 55.9, batch 32 18.2 against 18.9, batch 2
 //    9.6 against 6.0;
 //  - the pointwise kernel for 1x1 filters over 64 or 128 channels (256 without
-//    an addend) with a dense output of 128+ channels, from 65,536 output rows
-//    on: 28x28 128 -> 512 at batch 128 34.9 against 43.9, at batch 32 28.3
-//    against 14.8; 56x56 256 -> 128 69 against 77; 14x14 256 -> 1024 at batch
-//    128 (25,088 rows) 33.9 against 32-34.6;
-//  - the register-direct kernel for reductions up to 256 over 131,072 rows or
-//    more in one phase (56x56 256 -> 64 at batch 128 44.4 against 45.7, at
-//    batch 32, 100,352 rows, 16.7 against 14.2), and for the short phases (up
-//    to 512) of large strided data gradients;
+//    an addend) with a dense output of 128+ channels that fills 1,280 tiles of
+//    128 x 128 (384 over 64 channels): 28x28 128 -> 512 at batch 128 (3,136
+//    tiles) 34.9 against 43.9, at batch 32 (784) 28.3 against 14.8; 14x14 256
+//    -> 1024 at batch 128 (1,568) 33.0 against 39.3; 56x56 64 -> 256 at batch
+//    16 with an addend (784) 14.4 against 19.8, at batch 8 (392) 7.0 against
+//    8.0, at batch 6 (294) 6.9 against 6.7;
+//  - the register-direct kernel for reductions up to 256 in one phase (512
+//    where the channels are an odd multiple of 32) over as many tiles (512 up
+//    to 32 outputs): 14x14 256 -> 1024 data gradient at batch 128 with an addend
+//    46.2 against 51.8, at batch 64 (784 tiles) 28.8 against 25.7; 56x56 256
+//    -> 64 at batch 128 44.4 against 45.7, at batch 32 16.7 against 14.2;
+//    56x56 32 -> 32 3x3 at batch 128 31.5 against 46.2; and
+//    for the short phases (up to 512) of large strided data gradients;
 //  - the 128 x 128 DMA-staged kernel, two workgroups per CU, for the longer
 //    phases of strided data gradients while they are short against a
 //    workgroup's start and end (up to 1,023) and more than 512 tiles: 56x56
@@ -2122,21 +2127,23 @@ IgemmKind igemm_kind(const IgemmArgs& a) {
     if (t > maxT) maxT = t;
   }
   const int64_t act = (int64_t)a.N * a.Hi * a.Wi * a.Ci * 2;
+  const int64_t tiles = ceil_div64(rows, 128) * ceil_div(a.Co, a.Co <= 64 ? 64 : 128);
   {
     const IgemmPhase& p = a.ph[0];
     const bool ci_ok = a.Ci == 64 || a.Ci == 128 || (a.Ci == 256 && !a.addend);
     if (a.nphase == 1 && p.Rt == 1 && p.St == 1 && p.pad_h == 0 && p.pad_w == 0 &&
         p.oph == 0 && p.opw == 0 && a.os_h == 1 && a.os_w == 1 && a.OH == p.Ho &&
         a.OW == p.Wo && ci_ok && p.ldb == a.Ci && a.Co >= 128 &&
-        a.Co % 8 == 0 && a.ldo % 8 == 0 && act < ((int64_t)1 << 31) && rows >= 65536)
+        a.Co % 8 == 0 && a.ldo % 8 == 0 && act < ((int64_t)1 << 31) && tiles >= (a.Ci == 64 ? 384 : 1280))
       return IgemmKind::kPointwise;
   }
-  const int64_t tiles = ceil_div64(rows, 128) * ceil_div(a.Co, a.Co <= 64 ? 64 : 128);
   if (a.nphase > 1 && tiles > 512 && maxK < 1024) {
     if (a.Ci % 64 == 0 && maxK >= 576 && maxT <= 32) return IgemmKind::kDma;
     if (a.Ci % 32 == 0 && maxK <= 512) return IgemmKind::kDirect;
   }
-  if (a.nphase == 1 && a.Ci % 32 == 0 && maxK <= 256 && rows >= 131072) return IgemmKind::kDirect;
+  if (a.nphase == 1 && a.Ci % 32 == 0 && maxK <= (a.Ci % 64 == 0 ? 256 : 512) &&
+      tiles >= (a.Co <= 32 ? 512 : 1280))
+    return IgemmKind::kDirect;
   return IgemmKind::kWide;
 }
 
