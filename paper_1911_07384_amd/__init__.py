@@ -136,23 +136,52 @@ def _check(fn: str, status: int) -> None:
         raise Fp16Error(fn, status)
 
 
+_DTYPES = frozenset()  # the element types a buffer may have (filled at first use)
+
+
 def _ptr(t):
     if t is None:
         return None
     if isinstance(t, int):
         return t
-    import torch
-    if t.dtype not in (torch.float16, torch.float32, torch.uint8, torch.int32):
-        raise TypeError(f"expected float16/float32/uint8/int32 tensor, got {t.dtype}")
+    if t.dtype not in _DTYPES:
+        _check_dtype(t)
     if not t.is_contiguous():
         raise ValueError("tensor must be contiguous")
     return t.data_ptr()
 
 
+def _check_dtype(t) -> None:
+    global _DTYPES
+    import torch
+    _DTYPES = frozenset((torch.float16, torch.float32, torch.uint8, torch.int32))
+    if t.dtype not in _DTYPES:
+        raise TypeError(f"expected float16/float32/uint8/int32 tensor, got {t.dtype}")
+
+
+def _first_current_stream():
+    """The current stream of the current device; from the second call on asked
+    of torch's C++ side directly (torch.cuda.current_stream() builds a Stream
+    object, 2.8 us of the 7.9 us that a call took on the host; 4.3 us now)."""
+    global _current_stream
+    import torch
+    s = torch.cuda.current_stream().cuda_stream  # initialises the device, or raises
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    device = getattr(torch._C, "_cuda_getDevice", None)
+    if raw is not None and device is not None:
+        def current():
+            return raw(device())
+        if current() == s:
+            _current_stream = current
+    return s
+
+
+_current_stream = _first_current_stream
+
+
 def _stream(stream):
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream
+        return _current_stream()
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream

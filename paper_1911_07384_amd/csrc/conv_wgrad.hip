@@ -446,9 +446,9 @@ struct WCfg {
 // 28x28 128 -> 128 47.3 -> 42.3, 7x7 512 -> 512 53.4 -> 41.7 (256 x 128; 54 on
 // 128 x 128), 56x56 256 -> 512 1x1/2 49.8 -> 40.8, 14x14 256 -> 1024 28.6 ->
 // 26.1.
-// Fewer channels or columns: four waves (64 x 192 tiles cover a 3x3 64-channel
-// filter's 576 columns exactly, where 64 x 256 tiles left a quarter of the
-// third tile empty: conv2_x 60.4 -> 53.5 us).
+// Fewer channels or columns: four waves, the tile that pads the columns less
+// (64 x 192 tiles cover a 3x3 64-channel filter's 576 columns exactly, where
+// 64 x 256 tiles left a quarter of the third empty: conv2_x 60.4 -> 53.5 us).
 inline WCfg wgrad_choice(int K, int Nw, int64_t npix) {
   if (K > 64 && Nw > 64) {
     static constexpr int kShapes[3][2] = {{128, 128}, {256, 128}, {128, 256}};
@@ -470,10 +470,9 @@ inline WCfg wgrad_choice(int K, int Nw, int64_t npix) {
     return best;
   }
   if (K > 64) return {128, 64, 3};
-  if (Nw % 192 == 0) return {64, 192};
-  if (Nw >= 256) return {64, 256};
-  if (Nw >= 128) return {64, 128};
-  return {64, 64};
+  if (Nw <= 64) return {64, 64};
+  if (Nw <= 128) return {64, 128};
+  return ceil_div(Nw, 192) * 192 < ceil_div(Nw, 256) * 256 ? WCfg{64, 192} : WCfg{64, 256};
 }
 
 template <bool CGEN>
