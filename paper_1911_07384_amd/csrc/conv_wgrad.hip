@@ -472,7 +472,7 @@ inline WCfg wgrad_choice(int K, int Nw, int64_t npix) {
   if (K > 64) return {128, 64, 3};
   if (Nw <= 64) return {64, 64};
   if (Nw <= 128) return {64, 128};
-  return ceil_div(Nw, 192) * 192 < ceil_div(Nw, 256) * 256 ? WCfg{64, 192} : WCfg{64, 256};
+  return ceil_div(Nw, 192) * 192 < ceil_div(Nw, 256) * 256 ? WCfg{64, 192} : WCfg{64, 256, 3, 8};
 }
 
 template <bool CGEN>
@@ -480,6 +480,8 @@ void launch_wgrad7(const WCfg& cfg, dim3 grid, hipStream_t st, const WgradArgs& 
   if (cfg.NW == 8) {
     if (cfg.BM == 256)
       hipLaunchKernelGGL((wgrad7_kernel<256, 128, 4, 2, 3, CGEN>), grid, dim3(512), 0, st, a);
+    else if (cfg.BM == 64)
+      hipLaunchKernelGGL((wgrad7_kernel<64, 256, 2, 4, 3, CGEN>), grid, dim3(512), 0, st, a);
     else if (cfg.BN == 256)
       hipLaunchKernelGGL((wgrad7_kernel<128, 256, 2, 4, 3, CGEN>), grid, dim3(512), 0, st, a);
     else
@@ -488,8 +490,6 @@ void launch_wgrad7(const WCfg& cfg, dim3 grid, hipStream_t st, const WgradArgs& 
   }
   if (cfg.BM == 128)
     hipLaunchKernelGGL((wgrad7_kernel<128, 64, 2, 2, 3, CGEN>), grid, dim3(256), 0, st, a);
-  else if (cfg.BN == 256)
-    hipLaunchKernelGGL((wgrad7_kernel<64, 256, 1, 4, 2, CGEN>), grid, dim3(256), 0, st, a);
   else if (cfg.BN == 192)
     hipLaunchKernelGGL((wgrad7_kernel<64, 192, 2, 2, 2, CGEN>), grid, dim3(256), 0, st, a);
   else if (cfg.BN == 128)

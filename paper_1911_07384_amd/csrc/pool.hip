@@ -216,26 +216,49 @@ __global__ __launch_bounds__(kPT) void maxpool_bwd_s2(const uint8_t* __restrict_
 #pragma unroll
       for (int jj = 0; jj < 2; ++jj) {
         const int wc = 2 * b + jj;
-        double acc[8];
+        V8 o;
+        // a position reads (i + 1) * (jj + 1) windows: up to two terms are
+        // added in float32, whose one rounding on the way to binary16 changes
+        // nothing (24 >= 2 * 11 + 2 bits: Figueroa, "When is double rounding
+        // innocuous?", 1995; sums in the subnormal range are exact), four in
+        // float64
+        if (i + jj < 2) {
+          float acc[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) acc[e] = 0.0;
+          for (int e = 0; e < 8; ++e) acc[e] = 0.0f;
 #pragma unroll
-        for (int u = 0; u <= i; ++u)
+          for (int u = 0; u <= i; ++u)
 #pragma unroll
-          for (int w = 0; w <= jj; ++w) {
-            const int t = (1 + i - 2 * u) * 3 + (1 + jj - 2 * w);
+            for (int w = 0; w <= jj; ++w) {
+              const int t = (1 + i - 2 * u) * 3 + (1 + jj - 2 * w);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) {
-              const bool hit = ok[u][w] && (int)((taps[u][w] >> (8 * e)) & 0xFF) == t;
-              acc[e] += hit ? (double)to_f32(g[u][w].h[e]) : 0.0;
+              for (int e = 0; e < 8; ++e) {
+                const bool hit = ok[u][w] && (int)((taps[u][w] >> (8 * e)) & 0xFF) == t;
+                acc[e] += hit ? to_f32(g[u][w].h[e]) : 0.0f;
+              }
             }
-          }
-        if (h < a.H && wc < a.W) {
-          V8 o;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) o.h[e] = to_h16(acc[e]);
+        } else {
+          double acc[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) acc[e] = 0.0;
+#pragma unroll
+          for (int u = 0; u <= i; ++u)
+#pragma unroll
+            for (int w = 0; w <= jj; ++w) {
+              const int t = (1 + i - 2 * u) * 3 + (1 + jj - 2 * w);
+#pragma unroll
+              for (int e = 0; e < 8; ++e) {
+                const bool hit = ok[u][w] && (int)((taps[u][w] >> (8 * e)) & 0xFF) == t;
+                acc[e] += hit ? (double)to_f32(g[u][w].h[e]) : 0.0;
+              }
+            }
 #pragma unroll
           for (int e = 0; e < 8; ++e) o.h[e] = dbl_to_h16(acc[e]);
-          store16(dx + ((((int64_t)n * a.H + h) * a.W + wc) * CV + j) * 8, o);
         }
+        if (h < a.H && wc < a.W)
+          store16(dx + ((((int64_t)n * a.H + h) * a.W + wc) * CV + j) * 8, o);
       }
     }
   }
