@@ -89,6 +89,11 @@ ConvWs conv_ws(const ConvDims& d, int pass, int wg = 0) {
     off += align256(bytes);
     return at;
   };
+  // partial sums of `part` bytes (a multiple of 256) that fit the scratch array
+  // after the regions taken so far
+  auto room = [&](size_t part) {
+    return (int64_t)(off < kNoallocScratchBytes ? (kNoallocScratchBytes - off) / part : 0);
+  };
   const bool nchw = d.layout == FP16_NCHW;
   // a 1x1 filter over 1x1 images (a classifier) is a dense GEMM; with few
   // rows its reduction is split (float32 partials)
@@ -126,7 +131,8 @@ ConvWs conv_ws(const ConvDims& d, int pass, int wg = 0) {
   } else if (stem_s2d(d)) {
     L.need_x = true;
     L.x = take((size_t)d.N * d.P * d.Q * 16 * 2);
-    wgrad_plan(d.Kp, 16, 4, 4, (int64_t)d.N * d.P * d.Q, target, &L.splits, &L.pps);
+    wgrad_plan(d.Kp, 16, 4, 4, (int64_t)d.N * d.P * d.Q, target, room((size_t)d.Kp * 256 * 4),
+               &L.splits, &L.pps);
     L.part = take((size_t)L.splits * d.Kp * 256 * 4);
   } else {
     if (nchw || d.Cp != d.C) {
@@ -137,7 +143,8 @@ ConvWs conv_ws(const ConvDims& d, int pass, int wg = 0) {
       L.need_y = true;
       L.y = take((size_t)d.N * d.P * d.Q * d.Kp * 2);
     }
-    wgrad_plan(d.Kp, d.Cp, d.R, d.S, (int64_t)d.N * d.P * d.Q, target, &L.splits, &L.pps);
+    wgrad_plan(d.Kp, d.Cp, d.R, d.S, (int64_t)d.N * d.P * d.Q, target,
+               room((size_t)d.Kp * d.R * d.S * d.Cp * 4), &L.splits, &L.pps);
     L.part = take((size_t)L.splits * d.Kp * d.R * d.S * d.Cp * 4);
   }
   L.total = off;

@@ -500,7 +500,7 @@ void launch_wgrad7(const WCfg& cfg, dim3 grid, hipStream_t st, const WgradArgs& 
 
 }  // namespace
 
-void wgrad_plan(int K, int Cp, int R, int S, int64_t npix, int target, int* splits,
+void wgrad_plan(int K, int Cp, int R, int S, int64_t npix, int target, int64_t room, int* splits,
                 int* pix_per_split) {
   const int Nw = R * S * Cp;
   const WCfg cfg = wgrad_choice(K, Nw, npix);
@@ -514,9 +514,10 @@ void wgrad_plan(int K, int Cp, int R, int S, int64_t npix, int target, int* spli
   const int64_t max_splits = (npix + 4 * BKP - 1) / (4 * BKP);  // four k-steps each or more
   if (want > max_splits) want = max_splits;
   if (want < 1) want = 1;
-  int64_t pps = (npix + want - 1) / want;
-  pps = (pps + BKP - 1) / BKP * BKP;
-  if (pps < BKP) pps = BKP;
+  auto per_split = [&](int64_t n) { return ceil_div64(ceil_div64(npix, n), BKP) * BKP; };
+  int64_t pps = per_split(want);
+  const int64_t n = ceil_div64(npix, pps);
+  if (n > room && 2 * room >= n && room >= 1) pps = per_split(room);
   *pix_per_split = (int)pps;
   *splits = (int)((npix + pps - 1) / pps);
   if (*splits < 1) *splits = 1;

@@ -14,6 +14,7 @@
 // (two streams, two host threads) share the array and race.
 
 #include "../../include/fp16train.h"
+#include "kernels.hpp"
 
 #include <hip/hip_runtime.h>
 
@@ -21,7 +22,7 @@
 
 namespace {
 
-constexpr size_t kScratchBytes = (size_t)32 << 20;  // FP16_NOALLOC_SCRATCH_BYTES
+constexpr size_t kScratchBytes = fp16k::kNoallocScratchBytes;
 constexpr int kMaxDevices = 64;
 
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];

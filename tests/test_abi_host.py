@@ -295,6 +295,29 @@ def test_wgrad_noalloc_validates_before_touching_the_device():
     assert lib.fp16_conv_wgrad_noalloc(ctypes.byref(_conv()), A, None, Cc, None) == NULL
 
 
+# problems whose default number of splits needs up to 41 MiB, and which fit the
+# array of the scratch-free call with a few splits fewer
+NOALLOC_FITS = [
+    (50, 384, 9, 9, 768, 3, 1, "NCHW"),     # 3 splits 39.3 MiB, 2 splits 29.1
+    (50, 108, 28, 28, 1344, 3, 1, "NHWC"),  # channels padded: x staged beside the partial sums
+    (55, 792, 27, 27, 113, 3, 1, "NHWC"),   # dy staged
+    (8, 238, 54, 54, 100, 7, 1, "NHWC"),    # 5 splits 38.6 MiB, 3 fit
+    (98, 15, 36, 36, 57, 3, 1, "NHWC"),     # 497 splits 36.9 MiB, 358 fit
+    (57, 397, 8, 8, 250, 5, 1, "NCHW"),
+    (62, 147, 28, 28, 49, 7, 2, "NCHW"),
+]
+
+
+@pytest.mark.parametrize("shape", NOALLOC_FITS, ids=[str(s) for s in NOALLOC_FITS])
+def test_wgrad_noalloc_takes_what_fewer_splits_fit(shape):
+    n, c, h, w, k, r, st, lay = shape
+    lib = F.lib()
+    d = F.conv_desc(n, c, h, w, k, r, r, st, r // 2, lay)
+    assert F.fp16_conv_workspace_bytes(d, F.PASS_WGRAD) <= lib.fp16_noalloc_scratch_bytes()
+    # not refused for its size: the missing pointer is the error
+    assert lib.fp16_conv_wgrad_noalloc(ctypes.byref(d), A, None, Cc, None) == NULL
+
+
 # ---- pooling and loss: every call below is invalid, nothing is launched ---------
 
 UNSUPPORTED = 7

@@ -60,3 +60,43 @@ def test_noalloc_refuses_oversized_problem():
     st = lib.fp16_conv_wgrad_noalloc(ctypes.byref(d), t.data_ptr(), t.data_ptr(), t.data_ptr(),
                                      None)
     assert st == 6  # FP16_ERR_WORKSPACE
+
+
+# (n, c, h, k, r, layout): the default number of splits would not fit the
+# array; the plan takes what fits (2 of 3 splits, 3 of 5)
+FITTED = [(57, 397, 8, 250, 5, "NCHW"), (8, 238, 54, 100, 7, "NHWC")]
+
+
+@pytest.mark.parametrize("shape", FITTED, ids=[str(s) for s in FITTED])
+def test_noalloc_on_a_plan_cut_to_the_array(shape):
+    """Bit-identical to the call with a workspace, and every element within one
+    rounding to binary16 plus the float32 sums' M * 2^-24 * sum |a b| of float64."""
+    require_gpu()
+    n, c, h, k, r, lay = shape
+    pad, lib = r // 2, F.lib()
+    d = F.conv_desc(n, c, h, h, k, r, r, 1, pad, lay)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(85)
+    x = torch.randn((n, h, h, c), generator=g, device="cuda").half()
+    dy = torch.randn((n, h, h, k), generator=g, device="cuda").half()
+    last = (lambda t: t) if lay == "NHWC" else (lambda t: t.permute(0, 3, 1, 2).contiguous())
+    X, DY = last(x), last(dy)
+    shape_w = (k, r, r, c) if lay == "NHWC" else (k, c, r, r)
+    ref, got = (torch.full(shape_w, float("nan"), dtype=torch.float16, device="cuda")
+                for _ in range(2))
+    ws = F.workspace(F.fp16_conv_workspace_bytes(d, F.PASS_WGRAD))
+    note(f"[gpu] wgrad noalloc, fitted plan: {shape}")
+    F.fp16_conv_wgrad(d, X, DY, ref, ws)
+    F.fp16_conv_wgrad_noalloc(d, X, DY, got)
+    torch.cuda.synchronize()
+    assert torch.equal(got.view(torch.int16), ref.view(torch.int16))
+    w = got if lay == "NHWC" else got.permute(0, 2, 3, 1)
+    xp = torch.nn.functional.pad(x.double(), (0, 0, pad, pad, pad, pad))
+    flat = dy.double().reshape(-1, k).t().contiguous()
+    for i in range(r):
+        for j in range(r):
+            a = xp[:, i:i + h, j:j + h, :].reshape(-1, c)
+            want = flat @ a
+            bound = (want.abs() * 2.0 ** -11 + 2.0 ** -25 +
+                     (n * h * h + 2) * 2.0 ** -24 * (flat.abs() @ a.abs()))
+            assert ((w[:, i, j, :].double() - want).abs() / bound).max().item() <= 1.0, (i, j)
