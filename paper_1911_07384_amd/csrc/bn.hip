@@ -180,22 +180,23 @@ __global__ __launch_bounds__(kT) void bn_fwd_reduce_vec(const h16* __restrict__ 
     sums[1][e] = 0.0f;
   }
   // four rows in flight per thread, the sums row by row; the step count is
-  // the launch's, and a row past the last is loaded clamped (in bounds) and
-  // adds exact zeros, so no load waits behind a condition
+  // the launch's, and a row past the block's last is loaded clamped (in
+  // bounds) and adds exact zeros, so no load waits behind a condition
   const bool act = t < RB * CV;
-  const int64_t rt = (int64_t)blockIdx.x * RB + t / CV;
-  const int64_t RS = (int64_t)RB * gridDim.x;
+  const int64_t row0 = (int64_t)blockIdx.x * nsteps * RB;
+  const int64_t row1 = row0 + nsteps * RB < g.M ? row0 + nsteps * RB : g.M;
+  const int64_t rt = row0 + t / CV;
   for (int64_t i = 0; i < nsteps; i += 4) {
     V8 v[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const int64_t row = rt + (i + u) * RS;
-      v[u] = load16(x + (row < g.M ? row : g.M - 1) * g.C + j * 8);
+      const int64_t row = rt + (i + u) * RB;
+      v[u] = load16(x + (row < row1 ? row : row1 - 1) * g.C + j * 8);
     }
     __builtin_amdgcn_sched_barrier(0);  // every load issued before the first use
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const bool ok = act && rt + (i + u) * RS < g.M;
+      const bool ok = act && rt + (i + u) * RB < row1;
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const float d = ok ? to_f32(v[u].h[e]) - sh[e] : 0.0f;
@@ -544,18 +545,6 @@ constexpr int kSwap = 1, kRelu = 2, kMaskY = 4, kLoadR = 8, kDres = 16, kMaskB =
 // discarded).
 constexpr int kApplyU = 4;
 
-// The applies walk the tensor backwards (run r from the end): the pass before
-// them -- the reduce, whose workgroups advance through it together, or the
-// convolution that wrote x -- left the memory-side cache (256 MB) holding the
-// tensor's end.  What is read here for the last time in a long while (x in
-// the forward; x and dy in the backward) is loaded past that cache, and the
-// shortcut gradient stored past it, so that they do not push out what the
-// following calls read.  Measured at batch 128: the [56, 56, 256] layer's
-// backward with a kept mask 198 -> 178 us (interleaved reduce and backward
-// walk 9 us, the loads past the cache 11 us), the whole ResNet-50 step
-// 11.69 -> 11.52 ms; also loading the shortcut past the cache cost the BN swap
-// layer at [28, 28, 512] 19 us, and storing dx past it 6 us on the first.
-
 template <int MODE>
 __global__ __launch_bounds__(kT) void bn_fwd_apply_vec(const h16* x, const h16* __restrict__ gamma,
                                                        const h16* __restrict__ beta, const h16* res,
@@ -571,15 +560,13 @@ __global__ __launch_bounds__(kT) void bn_fwd_apply_vec(const h16* x, const h16* 
   for (int e = 0; e < 8; ++e) k[e] = fwd_coef(stats, gamma, beta, g.C, j * 8 + e, s);
   const int64_t nvec = g.M * CV;
   const int64_t RUN = (int64_t)kApplyU * TV;
-  const int64_t nruns = (nvec + RUN - 1) / RUN;
-  for (int64_t r = nruns - 1 - blockIdx.x; r >= 0; r -= gridDim.x) {
-    const int64_t run = r * RUN;
+  for (int64_t run = (int64_t)blockIdx.x * RUN; run < nvec; run += (int64_t)gridDim.x * RUN) {
     V8 xv[kApplyU], rv[kApplyU];
 #pragma unroll
     for (int u = 0; u < kApplyU; ++u) {
       const int64_t v = run + t + u * TV;
       const int64_t vc = v < nvec ? v : nvec - 1;
-      xv[u] = load16_last(x + vc * 8);
+      xv[u] = load16(x + vc * 8);
       if (HAS_R) rv[u] = load16(res + vc * 8);
     }
     __builtin_amdgcn_sched_barrier(0);  // every load issued before the first use
@@ -649,18 +636,19 @@ __global__ __launch_bounds__(kT) void bn_bwd_reduce_vec(const h16* __restrict__ 
     for (int v = 0; v < NS; ++v) sums[v][e] = 0.0f;
   }
   // one row per step, the next row loaded before this one is summed (two rows
-  // in flight); the step count is the block's, and a row past the block's
+  // in flight); the step count is the launch's, and a row past the block's
   // last is loaded clamped (in bounds) and adds exact zeros
   struct Row {
     V8 x, d, y, r;
     uint32_t mb;
   };
   const bool act = t < RB * CV;
-  const int64_t rt = (int64_t)blockIdx.x * RB + t / CV;
-  const int64_t RS = (int64_t)RB * gridDim.x;
+  const int64_t row0 = (int64_t)blockIdx.x * nsteps * RB;
+  const int64_t row1 = row0 + nsteps * RB < g.M ? row0 + nsteps * RB : g.M;
+  const int64_t rt = row0 + t / CV;
   auto load_row = [&](Row& b, int64_t i) {
-    int64_t row = rt + i * RS;
-    if (row >= g.M) row = g.M - 1;
+    int64_t row = rt + i * RB;
+    if (row >= row1) row = row1 - 1;
     const int64_t off = row * g.C + j * 8;
     b.x = load16(x + off);
     b.d = load16(dy + off);
@@ -669,7 +657,7 @@ __global__ __launch_bounds__(kT) void bn_bwd_reduce_vec(const h16* __restrict__ 
     if (MASK_B) b.mb = mbits[row * CV + j];
   };
   auto sum_row = [&](const Row& b, int64_t i) {
-    const bool ok = act && rt + i * RS < g.M;
+    const bool ok = act && rt + i * RB < row1;
     uint32_t bits = 0;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
@@ -685,7 +673,7 @@ __global__ __launch_bounds__(kT) void bn_bwd_reduce_vec(const h16* __restrict__ 
       sums[1][e] = __builtin_fmaf(gg, xt, sums[1][e]);
       if (SWAP) sums[NS - 1][e] = __builtin_fmaf(gg, ok ? rf : 0.0f, sums[NS - 1][e]);
     }
-    if (KEEP_M && ok) mbits[(rt + i * RS) * CV + j] = (uint8_t)bits;
+    if (KEEP_M && ok) mbits[(rt + i * RB) * CV + j] = (uint8_t)bits;
   };
   Row ra, rb;
   load_row(ra, 0);
@@ -816,17 +804,15 @@ __global__ __launch_bounds__(kT) void bn_bwd_apply_vec(const h16* x, const h16* 
   const int64_t nvec = g.M * CV;
   constexpr int U = kApplyU / 2;  // vectors per thread and run: 2 to 4 loads each
   const int64_t RUN = (int64_t)U * TV;
-  const int64_t nruns = (nvec + RUN - 1) / RUN;
-  for (int64_t r = nruns - 1 - blockIdx.x; r >= 0; r -= gridDim.x) {
-    const int64_t run = r * RUN;
+  for (int64_t run = (int64_t)blockIdx.x * RUN; run < nvec; run += (int64_t)gridDim.x * RUN) {
     V8 xv[U], dv[U], yv[U];
     uint32_t mb[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int64_t v = run + t + u * TV;
       const int64_t vc = v < nvec ? v : nvec - 1;
-      xv[u] = load16_last(x + vc * 8);
-      dv[u] = load16_last(dy + vc * 8);
+      xv[u] = load16(x + vc * 8);
+      dv[u] = load16(dy + vc * 8);
       if (MASK_Y) yv[u] = load16(y + vc * 8);
       if (NEED_R) mb[u] = mbits[vc];
     }
@@ -850,7 +836,7 @@ __global__ __launch_bounds__(kT) void bn_bwd_apply_vec(const h16* x, const h16* 
       }
       if (t < TV && v < nvec) {
         store16(dx + v * 8, o);
-        if (DRES) store16_far(dres + v * 8, od);
+        if (DRES) store16(dres + v * 8, od);
       }
     }
   }

@@ -29,16 +29,6 @@ __device__ __forceinline__ void store16(void* p, const V8& v) {
   *reinterpret_cast<u32x4*>(p) = v.u;
 }
 
-// The same past the caches (nontemporal): for data nothing reads again soon.
-__device__ __forceinline__ V8 load16_last(const void* p) {
-  V8 v;
-  v.u = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
-  return v;
-}
-__device__ __forceinline__ void store16_far(void* p, const V8& v) {
-  __builtin_nontemporal_store(v.u, reinterpret_cast<u32x4*>(p));
-}
-
 __device__ __forceinline__ V8 zero8() {
   V8 v;
   v.u = u32x4{0u, 0u, 0u, 0u};
