@@ -22,7 +22,7 @@
 // chunks of a workgroup idle where C/8 is not a power of two), so every access
 // is a 16-byte vector and per-channel coefficients are computed once per
 // thread.  NCHW takes chunks of 8 pixels of one channel.  Other channel counts
-// use a generic per-element path.
+// and the smallest NCHW images use a generic per-element path.
 // Reductions are float32 within a thread, combined in a fixed order within a
 // block and in float64 across blocks: the result does not depend on timing.
 
@@ -49,6 +49,10 @@ __device__ __forceinline__ int64_t geo_at(const Geo& g, int c, int64_t j) {
   const int64_t n = j / g.HW;
   return (n * g.C + c) * g.HW + (j - n * g.HW);
 }
+// channel of memory index i
+__device__ __forceinline__ int geo_chan(const Geo& g, int64_t i) {
+  return g.layout == 0 ? (int)(i % g.C) : (int)((i / g.HW) % g.C);
+}
 
 struct Plan {
   // NHWC, 8-channel chunks: C % 8 == 0, C <= 2048 ([1, 100, 100, 1952] with a
@@ -61,12 +65,23 @@ struct Plan {
   int64_t rpb;    // generic and NCHW reduces: elements or chunks per block
 };
 
+// Whether an NCHW tensor goes in chunks of 8 pixels, else one element per
+// thread: images under 16 pixels are half padding as chunks ([256, 2048, 2, 2]
+// forward 16.8 us by elements, 33.6 in chunks), and with few pixels a channel a
+// chunk's longer body costs more than it saves ([1, 3, 7, 7] backward with a
+// shortcut 7.0 and 8.9 us, [4, 3, 6, 6] 7.7 and 8.6; from 256 pixels on chunks
+// are as fast or faster).
+bool nchw_chunks_pay(const BnArgs& a) {
+  const int64_t HW = (int64_t)a.H * a.W;
+  return HW >= 16 && a.N * HW >= 256;
+}
+
 Plan make_plan(const BnArgs& a) {
   Plan p{};
   const int64_t M = (int64_t)a.N * a.H * a.W;
   const int CV = a.C / 8;
   p.vec = a.layout == 0 && a.C % 8 == 0 && CV >= 1 && CV <= kT;
-  p.nchw = a.layout != 0;
+  p.nchw = a.layout != 0 && nchw_chunks_pay(a);
   if (p.vec) {
     p.CV = CV;
     p.RB = kT / CV;
@@ -596,7 +611,7 @@ __global__ __launch_bounds__(kT) void bn_fwd_apply_gen(const h16* x, const h16* 
   const int64_t total = g.M * g.C;
   for (int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x; i < total;
        i += (int64_t)gridDim.x * kT) {
-    const int c = (int)(i % g.C);
+    const int c = geo_chan(g, i);
     const FwdCoef k = fwd_coef(stats, gamma, beta, g.C, c, s);
     y[i] = to_h16(fwd_value(to_f32(x[i]), k, res != nullptr, res ? to_f32(res[i]) : 0.0f,
                             relu != 0, g.swap != 0));
@@ -853,7 +868,7 @@ __global__ __launch_bounds__(kT) void bn_bwd_apply_gen(const h16* x, const h16* 
   const bool has_y = y != nullptr, has_r = res != nullptr && !has_y && relu;
   for (int64_t i = (int64_t)blockIdx.x * kT + threadIdx.x; i < total;
        i += (int64_t)gridDim.x * kT) {
-    const int c = (int)(i % g.C);
+    const int c = geo_chan(g, i);
     const FwdCoef k = fwd_coef(stats, gamma, beta, g.C, c, s);
     const float xf = to_f32(x[i]);
     const h16 dyv = dy[i];
@@ -868,20 +883,25 @@ __global__ __launch_bounds__(kT) void bn_bwd_apply_gen(const h16* x, const h16* 
 // ---- NCHW -------------------------------------------------------------------------
 // A channel's elements are N runs of HW values.  Chunks of 8 consecutive
 // values of one run (the run's last may be partial; runs start at any 2-byte
-// alignment) are read and written 16 bytes at a time.  The reduces take one
+// alignment) are read and, whole ones, written 16 bytes at a time.  The reduces take one
 // channel and a range of its chunks per workgroup, four chunks per thread in
 // flight; the applies one chunk per thread and step.  ([32, 256, 28, 28],
 // forward and backward: 66.6 us one element per thread, 33.5 now, the
 // six launches a third of it.)
 __device__ __forceinline__ V8 chunk_load(const h16* p, int left) {
-  V8 v;
-  if (left >= 8) {
-    __builtin_memcpy(&v, p, 16);
-  } else {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) v.h[e] = e < left ? p[e] : (h16)0.0f;
-  }
-  return v;
+  // a partial chunk (HW >= 16, so never a run's first): the run's last 8
+  // values, shifted down; zeros past the run
+  union {
+    V8 v;
+    uint64_t q[2];
+  } u;
+  const int over = left >= 8 ? 0 : 8 - left;
+  __builtin_memcpy(&u.v, p - over, 16);
+  const int sh = 16 * (over & 3);
+  const uint64_t lo = over & 4 ? u.q[1] : u.q[0], hi = over & 4 ? 0 : u.q[1];
+  u.q[0] = lo >> sh | (hi << 1) << (63 - sh);
+  u.q[1] = hi >> sh;
+  return u.v;
 }
 __device__ __forceinline__ void chunk_store(h16* p, int left, const V8& v) {
   if (left >= 8) {

@@ -19,7 +19,12 @@ EPS, SCALE = 1e-5, 0.25
 # (n, c, h, w)
 SHAPES = [(2, 24, 5, 3), (3, 160, 9, 7), (2, 72, 14, 14), (1, 1000, 3, 5), (5, 136, 1, 1),
           (2, 2040, 2, 2), (4, 40, 33, 31), (3, 16, 7, 7), (2, 5, 4, 2), (1, 7, 61, 67),
-          (40, 8, 8, 16), (3, 264, 28, 28)]
+          (40, 8, 8, 16), (3, 264, 28, 28),
+          # NCHW in chunks: every remainder of a run, the smallest image and count
+          (6, 9, 7, 7), (15, 3, 2, 9), (8, 4, 5, 7), (14, 6, 4, 5), (13, 3, 1, 21), (9, 5, 5, 6),
+          (16, 3, 4, 4), (1, 3, 16, 16),
+          # ... and one element per thread just below
+          (1, 3, 15, 17), (40, 5, 3, 5)]
 
 
 @pytest.mark.parametrize("form", ["plain", "residual", "stored", "norelu", "swap"])
