@@ -17,6 +17,34 @@ inline unsigned grid_for(int64_t n) {
   return (unsigned)b;
 }
 
+// dst[n][hw][c] = c < C ? src[n][c][hw] : 0, for c < Cp.
+__global__ void nchw_to_nhwc_kernel(const h16* __restrict__ src, h16* __restrict__ dst, int N,
+                                    int C, int HW, int Cp) {
+  const int64_t total = (int64_t)N * HW * Cp;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total;
+       i += (int64_t)gridDim.x * blockDim.x) {
+    const int c = (int)(i % Cp);
+    const int64_t t = i / Cp;
+    const int hw = (int)(t % HW);
+    const int64_t n = t / HW;
+    dst[i] = c < C ? src[(n * C + c) * HW + hw] : (h16)0.0f;
+  }
+}
+
+// dst[n][c][hw] = src[n][hw][c] for c < C.
+__global__ void nhwc_to_nchw_kernel(const h16* __restrict__ src, h16* __restrict__ dst, int N,
+                                    int C, int HW, int Cp) {
+  const int64_t total = (int64_t)N * C * HW;
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total;
+       i += (int64_t)gridDim.x * blockDim.x) {
+    const int hw = (int)(i % HW);
+    const int64_t t = i / HW;
+    const int c = (int)(t % C);
+    const int64_t n = t / C;
+    dst[i] = src[(n * HW + hw) * Cp + c];
+  }
+}
+
 // Eight consecutive values at any 2-byte alignment (one 16-byte access).
 __device__ __forceinline__ V8 load8u(const h16* p) {
   V8 v;
@@ -263,13 +291,39 @@ static hipError_t launch_transpose(const h16* src, h16* dst, int N, int rows, in
   return hipGetLastError();
 }
 
+// Whether a conversion of N images of C channels and HW pixels goes in 8 x 8
+// blocks or element by element.  A block kernel whose blocks are all whole
+// takes 2.2 to 3.4 us up to the size where one element per thread is no longer
+// hidden by the launch (a quarter to half a million elements: [64, 64, 8, 8]
+// 2.7 us element, 3.3 block; [64, 512, 4, 4] 3.2 and 3.0; [16, 64, 28, 28] 3.9
+// and 3.4); with partial blocks, moved value by value, about 5 us ([16, 128, 3,
+// 3] filter 2.4 and 5.0; [64, 512, 5, 5] 3.8 and 5.7; [256, 64, 10, 10] 5.5 and
+// 5.3; [64, 512, 7, 7] 7.4 and 6.1).  Fewer than 8 pixels, or channels to be
+// written one plane each, leave most of a block empty ([1024, 2048, 2, 2] 19.2
+// and 25.4; [1024, 3, 40, 40] to NCHW 15.7 and 17.7).
+static bool blocks_pay(int64_t N, int C, int HW, bool to_nchw) {
+  if (HW < 8 || (to_nchw && C < 8)) return false;
+  const bool whole = HW % 8 == 0 && C % 8 == 0;
+  return N * C * HW >= (whole ? 3 << 17 : 1 << 20);
+}
+
 hipError_t launch_nchw_to_nhwc(const h16* src, h16* dst, int N, int C, int HW, int Cp,
                                hipStream_t st) {
+  if (!blocks_pay(N, C, HW, false)) {
+    hipLaunchKernelGGL(nchw_to_nhwc_kernel, dim3(grid_for((int64_t)N * HW * Cp)), dim3(kThreads),
+                       0, st, src, dst, N, C, HW, Cp);
+    return hipGetLastError();
+  }
   return launch_transpose(src, dst, N, C, HW, HW, Cp, st);
 }
 
 hipError_t launch_nhwc_to_nchw(const h16* src, h16* dst, int N, int C, int HW, int Cp,
                                hipStream_t st) {
+  if (!blocks_pay(N, C, HW, true)) {
+    hipLaunchKernelGGL(nhwc_to_nchw_kernel, dim3(grid_for((int64_t)N * C * HW)), dim3(kThreads), 0,
+                       st, src, dst, N, C, HW, Cp);
+    return hipGetLastError();
+  }
   return launch_transpose(src, dst, N, HW, C, Cp, HW, st);
 }
 

@@ -1,7 +1,7 @@
 """NCHW calls move their tensors through the library's layout conversions: a
 1x1 convolution with the identity filter returns its input bit for bit, and
 its gradients the output gradient, at sizes around the conversions' 8 x 8
-blocks and the runs of one wave."""
+blocks and the runs of one wave, and below the size from which blocks are used."""
 
 import pytest
 import torch
@@ -12,7 +12,13 @@ from gpu_util import require_gpu
 pytestmark = pytest.mark.gpu
 
 SHAPES = [(1, 8, 1, 1), (3, 24, 5, 3), (2, 65, 7, 9), (1, 130, 16, 16), (2, 9, 31, 1),
-          (4, 64, 8, 8), (1, 3, 33, 2), (2, 512, 7, 7), (1, 72, 9, 57), (5, 1, 3, 3)]
+          (4, 64, 8, 8), (1, 3, 33, 2), (2, 512, 7, 7), (1, 72, 9, 57), (5, 1, 3, 3),
+          # from here on in blocks (the smaller ones element by element): all
+          # blocks whole, then partial in pixels, in channels and in both
+          (3, 64, 48, 48), (96, 64, 8, 8), (330, 136, 5, 5), (17, 1030, 8, 8), (3, 65, 75, 73),
+          (2, 9, 241, 245), (130, 904, 3, 3),
+          # 3 channels: to NHWC in blocks, back element by element
+          (20, 3, 133, 137)]
 
 
 @pytest.mark.parametrize("shape", SHAPES, ids=["x".join(map(str, s)) for s in SHAPES])
