@@ -469,6 +469,14 @@ fp16_status fp16_softmax_ce(int32_t n, int32_t k, const fp16_t* z, const fp16_t*
                             const int32_t* labels, float* loss, fp16_t* dz, fp16_t* dbias,
                             fp16_stream_t stream);
 
+/* The kernel a convolution pass runs on and its tile, e.g. "wide 224x128", for
+ * tests and profiles; "" for an invalid descriptor.  form: FP16_FORM_ADDEND
+ * for a data gradient with an addend, FP16_FORM_STATS for the forward of
+ * fp16_conv_bn_relu_fwd (its first launch), else 0.  The names are no contract.
+ * The string is the calling thread's, valid until its next call. */
+enum { FP16_FORM_ADDEND = 1, FP16_FORM_STATS = 2 };
+const char* fp16_conv_kernel(const fp16_conv_desc* desc, int32_t pass, int32_t form);
+
 /* Human-readable name of a status code (static string). */
 const char* fp16_status_string(fp16_status status);
 

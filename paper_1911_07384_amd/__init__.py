@@ -34,7 +34,7 @@ EXPORTS = ["fp16_conv_out_dims", "fp16_conv_workspace_bytes", "fp16_conv_fwd", "
            "fp16_version", "fp16_conv_bn_workspace_bytes", "fp16_conv_bn_relu_fwd",
            "fp16_sgd_step_f16", "fp16_conv_dgrad_filter_bytes", "fp16_conv_dgrad_filter",
            "fp16_conv_dgrad_filters",
-           "fp16_conv_dgrad_wf", "fp16_noalloc_scratch_bytes", "fp16_conv_wgrad_noalloc",
+           "fp16_conv_dgrad_wf", "fp16_conv_kernel", "fp16_noalloc_scratch_bytes", "fp16_conv_wgrad_noalloc",
            "fp16_bn_mask_bytes", "fp16_bn_relu_m", "fp16_bn_relu_bwd_m", "fp16_conv_bn_relu_fwd_m",
            "fp16_conv_dgrad_wf_m", "fp16_bn_relu_maxpool", "fp16_conv_wgrad_ex",
            "fp16_conv_dgrad_wf_ex"]
@@ -103,6 +103,7 @@ _SIGS = {
     "fp16_softmax_ce": (ctypes.c_int, [_I32, _I32, _P, _P, _P, _P, _P, _P, _P]),
     "fp16_conv_bn_workspace_bytes": (_SZ, [_P, _P]),
     "fp16_conv_bn_relu_fwd": (ctypes.c_int, [_P] * 11 + [_SZ, _P]),
+    "fp16_conv_kernel": (ctypes.c_char_p, [_P, _I32, _I32]),
     "fp16_status_string": (ctypes.c_char_p, [ctypes.c_int]),
     "fp16_version": (ctypes.c_char_p, []),
 }
@@ -215,6 +216,12 @@ def fp16_conv_out_dims(desc: ConvDesc):
     _check("fp16_conv_out_dims", lib().fp16_conv_out_dims(ctypes.byref(desc), ctypes.byref(p),
                                                           ctypes.byref(q)))
     return p.value, q.value
+
+
+def fp16_conv_kernel(desc: ConvDesc, pass_: int, addend: bool = False, stats: bool = False) -> str:
+    """The kernel a pass runs on and its tile (for tests and profiles)."""
+    return lib().fp16_conv_kernel(ctypes.byref(desc), int(pass_),
+                                  int(addend) + 2 * int(stats)).decode()
 
 
 def fp16_conv_workspace_bytes(desc: ConvDesc, pass_: int) -> int:

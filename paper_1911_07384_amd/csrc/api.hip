@@ -162,6 +162,54 @@ IgemmArgs stem_args(const ConvDims& d, const h16* x, const h16* w, h16* y) {
   return a;
 }
 
+// The forward's problem over NHWC x with Cp channels and the KRSC filter.
+IgemmArgs fwd_args(const ConvDims& d, const h16* x, const h16* w, h16* y) {
+  IgemmArgs a{};
+  a.act = x; a.N = d.N; a.Hi = d.H; a.Wi = d.W; a.Ci = d.Cp;
+  a.stride_h = d.sh; a.stride_w = d.sw;
+  a.Co = d.K; a.out = y; a.OH = d.P; a.OW = d.Q; a.ldo = d.K; a.os_h = 1; a.os_w = 1;
+  a.nphase = 1;
+  a.ph[0] = IgemmPhase{w, d.R * d.S * d.Cp, d.R, d.S, d.ph, d.pw, d.P, d.Q, 0, 0};
+  return a;
+}
+
+// The data gradient's problem over NHWC dy with Kp channels, without phases.
+IgemmArgs dgrad_args(const ConvDims& d, const h16* dy, const h16* addend, const uint8_t* amask,
+                     int astride, h16* dx) {
+  IgemmArgs a{};
+  a.act = dy; a.N = d.N; a.Hi = d.P; a.Wi = d.Q; a.Ci = d.Kp;
+  a.stride_h = 1; a.stride_w = 1;
+  a.Co = d.C; a.out = dx; a.OH = d.H; a.OW = d.W; a.ldo = d.C; a.os_h = d.sh; a.os_w = d.sw;
+  a.addend = addend;
+  a.amask = amask;
+  a.astride = astride;
+  return a;
+}
+
+// Its launches: the stride phases with any output, four at a time, from the
+// rearranged filter wf (each phase's taps in turn); stops at the first error.
+template <typename Launch>
+hipError_t dgrad_launches(const ConvDims& d, IgemmArgs a, const h16* wf, Launch launch) {
+  a.nphase = 0;
+  int64_t off = 0;
+  for (int ph = 0; ph < d.sh; ++ph) {
+    for (int pw = 0; pw < d.sw; ++pw) {
+      const DgradPhase g = dgrad_phase(ph, pw, d.H, d.W, d.R, d.S, d.sh, d.sw, d.ph, d.pw);
+      if (g.Hph > 0 && g.Wph > 0) {
+        a.ph[a.nphase++] = IgemmPhase{wf + off, g.ntr * g.nts * d.Kp, g.ntr, g.nts, g.pad_h,
+                                      g.pad_w, g.Hph, g.Wph, ph, pw};
+        if (a.nphase == 4) {
+          const hipError_t e = launch(a);
+          if (e != hipSuccess) return e;
+          a.nphase = 0;
+        }
+      }
+      off += (int64_t)d.C * g.ntr * g.nts * d.Kp;
+    }
+  }
+  return a.nphase > 0 ? launch(a) : hipSuccess;
+}
+
 ConvChainArgs chain_args(const ConvDims& d) {
   return ConvChainArgs{d.N, d.C, d.H, d.W, d.K, d.R, d.S, d.sh, d.sw, d.ph, d.pw, d.P, d.Q};
 }
@@ -256,12 +304,7 @@ fp16_status fp16_conv_fwd(const fp16_conv_desc* desc, const fp16_t* x, const fp1
     xe = wsp(ws, L.x);
     we = wsp(ws, L.w);
   }
-  IgemmArgs a{};
-  a.act = xe; a.N = d.N; a.Hi = d.H; a.Wi = d.W; a.Ci = d.Cp;
-  a.stride_h = d.sh; a.stride_w = d.sw;
-  a.Co = d.K; a.out = ye; a.OH = d.P; a.OW = d.Q; a.ldo = d.K; a.os_h = 1; a.os_w = 1;
-  a.nphase = 1;
-  a.ph[0] = IgemmPhase{we, d.R * d.S * d.Cp, d.R, d.S, d.ph, d.pw, d.P, d.Q, 0, 0};
+  IgemmArgs a = fwd_args(d, xe, we, ye);
   if (L.splits > 1) {  // a dense GEMM with its reduction split
     a.part = reinterpret_cast<float*>(static_cast<char*>(ws) + L.part);
     a.splits = L.splits;
@@ -338,34 +381,14 @@ static fp16_status conv_dgrad_impl(const fp16_conv_desc* desc, const fp16_t* dy,
     TRY(launch_dgrad_filter(wk, wt, d.K, d.C, d.R, d.S, d.C, d.Kp, d.sh, d.sw, d.ph, d.pw, st));
     wf = wt;
   }
-  IgemmArgs a{};
-  a.act = dye; a.N = d.N; a.Hi = d.P; a.Wi = d.Q; a.Ci = d.Kp;
-  a.stride_h = 1; a.stride_w = 1;
-  a.Co = d.C; a.out = dxe; a.OH = d.H; a.OW = d.W; a.ldo = d.C; a.os_h = d.sh; a.os_w = d.sw;
-  a.addend = addend ? (d.layout == FP16_NCHW ? dxe : reinterpret_cast<const h16*>(addend)) : nullptr;
-  a.amask = amask;
-  a.astride = astride;
+  IgemmArgs a = dgrad_args(
+      d, dye, addend ? (d.layout == FP16_NCHW ? dxe : reinterpret_cast<const h16*>(addend)) : nullptr,
+      amask, astride, dxe);
   if (L.splits > 1 && !amask && astride == 1) {  // a dense GEMM with its reduction split
     a.part = reinterpret_cast<float*>(static_cast<char*>(ws) + L.part);
     a.splits = L.splits;
   }
-  a.nphase = 0;
-  int64_t off = 0;
-  for (int ph = 0; ph < d.sh; ++ph) {
-    for (int pw = 0; pw < d.sw; ++pw) {
-      const DgradPhase g = dgrad_phase(ph, pw, d.H, d.W, d.R, d.S, d.sh, d.sw, d.ph, d.pw);
-      if (g.Hph > 0 && g.Wph > 0) {
-        a.ph[a.nphase++] = IgemmPhase{wf + off, g.ntr * g.nts * d.Kp, g.ntr, g.nts, g.pad_h,
-                                      g.pad_w, g.Hph, g.Wph, ph, pw};
-        if (a.nphase == 4) {
-          TRY(launch_igemm(a, st));
-          a.nphase = 0;
-        }
-      }
-      off += (int64_t)d.C * g.ntr * g.nts * d.Kp;
-    }
-  }
-  if (a.nphase > 0) TRY(launch_igemm(a, st));
+  TRY(dgrad_launches(d, a, wf, [&](const IgemmArgs& g) { return launch_igemm(g, st); }));
   if (d.layout == FP16_NCHW)
     TRY(launch_nhwc_to_nchw(dxe, reinterpret_cast<h16*>(dx), d.N, d.C, d.H * d.W, d.C, st));
   return FP16_OK;
@@ -981,13 +1004,7 @@ static fp16_status conv_bn_impl(const fp16_conv_desc* conv, const fp16_bn_desc* 
     xe = wsp(ws, L.x);
     we = wsp(ws, L.w);
   }
-  IgemmArgs a{};
-  a.act = xe; a.N = d.N; a.Hi = d.H; a.Wi = d.W; a.Ci = d.Cp;
-  a.stride_h = d.sh; a.stride_w = d.sw;
-  a.Co = d.K; a.out = reinterpret_cast<h16*>(y); a.OH = d.P; a.OW = d.Q; a.ldo = d.K;
-  a.os_h = 1; a.os_w = 1;
-  a.nphase = 1;
-  a.ph[0] = IgemmPhase{we, d.R * d.S * d.Cp, d.R, d.S, d.ph, d.pw, d.P, d.Q, 0, 0};
+  IgemmArgs a = fwd_args(d, xe, we, reinterpret_cast<h16*>(y));
   const h16* gp = reinterpret_cast<const h16*>(gamma);
   const h16* bp = reinterpret_cast<const h16*>(beta);
   const h16* rp = reinterpret_cast<const h16*>(residual);
@@ -1047,6 +1064,50 @@ fp16_status fp16_conv_bn_relu_fwd_m(const fp16_conv_desc* conv, const fp16_bn_de
                                     size_t ws_bytes, fp16_stream_t stream) {
   return conv_bn_impl(conv, bn, x, w, gamma, beta, residual, y, z, stats, mask, true, ws,
                       ws_bytes, stream);
+}
+
+// ---- the kernel a pass runs on ----------------------------------------------------
+
+const char* fp16_conv_kernel(const fp16_conv_desc* desc, int32_t pass, int32_t form) {
+  thread_local char name[48];
+  ConvDims d;
+  if (check_conv(desc, &d) != FP16_OK || pass < FP16_PASS_FWD || pass > FP16_PASS_WGRAD ||
+      form < 0 || form > (FP16_FORM_ADDEND | FP16_FORM_STATS))
+    return "";
+  if (d.accum) return "chains";
+  // (the choice goes by shapes, and by whether these pointers are there)
+  h16* const some = reinterpret_cast<h16*>(256);
+  const ConvWs L = conv_ws(d, pass);
+  IgemmArgs a{};
+  if (pass == FP16_PASS_FWD) {
+    const IgemmArgs sa = stem_args(d, some, some, some);
+    if (d.layout == FP16_NHWC && stem_conv_ok(sa)) return "stem";
+    a = fwd_args(d, some, some, some);
+    if ((form & FP16_FORM_STATS) && igemm_stats_pay(a)) {
+      a.stat = reinterpret_cast<float*>(some);
+      a.stat_nb = igemm_stat_records(a);
+    }
+  } else if (pass == FP16_PASS_DGRAD) {
+    IgemmArgs first{};
+    const h16* addend = form & FP16_FORM_ADDEND ? some : nullptr;
+    (void)dgrad_launches(d, dgrad_args(d, some, addend, nullptr, 1, some), some,
+                         [&](const IgemmArgs& g) {
+                           if (first.nphase == 0) first = g;
+                           return hipSuccess;
+                         });
+    a = first;
+  } else {
+    const bool s2d = stem_s2d(d);
+    wgrad_name(d.Kp, s2d ? 16 : d.Cp, s2d ? 4 : d.R, s2d ? 4 : d.S, (int64_t)d.N * d.P * d.Q, name,
+               sizeof(name));
+    return name;
+  }
+  if (L.splits > 1) {
+    a.part = reinterpret_cast<float*>(some);
+    a.splits = L.splits;
+  }
+  igemm_name(a, name, sizeof(name));
+  return name;
 }
 
 }  // extern "C"

@@ -54,6 +54,8 @@
 
 #include "kernels.hpp"
 
+#include <stdio.h>
+
 #include <type_traits>
 
 
@@ -118,6 +120,223 @@ __device__ __forceinline__ void xcd_tile(int gn, int& z, int& mt, int& nt) {
   const int gw = NT - g * gn < gn ? NT - g * gn : gn;
   nt = g * gn + w % gw;
   mt = w / gw;
+}
+
+// ---- both operands through registers into LDS, any multiple of 8 channels -----
+// Four waves of a small tile at two workgroups per CU, double-buffered: for the
+// strided data gradients whose phases are so short (or empty) that a call is
+// the writing of its output, where the wide kernel's one workgroup per CU has
+// nothing to hide its start and its stores behind (see igemm_kind).
+template <int BM, int BN, int WM, int WN, int BK>
+struct Cfg {
+  static constexpr int LDK = BK + 8;
+  static constexpr int KC = BK / 8;           // 16-byte chunks per tile row
+  static constexpr int RSTEP = 256 / KC;      // rows covered per load pass
+  static constexpr int WTM = BM / WM, WTN = BN / WN;
+  static constexpr int TM = WTM / 32, TN = WTN / 32;
+  static constexpr int A_IT = BM / RSTEP;
+  static constexpr int B_IT = BN / RSTEP;
+  static constexpr int SP = WTN + 4;
+  static constexpr int MAIN_BYTES = 2 * (BM + BN) * LDK * 2;
+  static constexpr int STAGE_BYTES = 4 * 32 * SP * 4;
+  static constexpr int LDS_BYTES = MAIN_BYTES > STAGE_BYTES ? MAIN_BYTES : STAGE_BYTES;
+};
+
+template <int BM, int BN, int WM, int WN, int BK>
+__global__ __launch_bounds__(256) void igemm_kernel(const IgemmArgs a) {
+  using K = Cfg<BM, BN, WM, WN, BK>;
+  constexpr int LDK = K::LDK, KC = K::KC, RSTEP = K::RSTEP;
+  constexpr int WTM = K::WTM, WTN = K::WTN, TM = K::TM, TN = K::TN;
+  constexpr int A_IT = K::A_IT, B_IT = K::B_IT;
+  static_assert(WM * WN == 4, "four waves");
+  static_assert(TM >= 1 && TN >= 1 && A_IT >= 1 && B_IT >= 1, "tile shape");
+
+  __shared__ __attribute__((aligned(16))) char smem[K::LDS_BYTES];
+  h16* As = reinterpret_cast<h16*>(smem);
+  h16* Bs = As + 2 * BM * LDK;
+
+  int tz, tm_, tn_;
+  xcd_tile(a.gn, tz, tm_, tn_);
+  const IgemmPhase ph = a.ph[tz];
+  const int HoWo = ph.Ho * ph.Wo;
+  const int M = a.N * HoWo;
+  const int m0 = tm_ * BM;
+  if (m0 >= M) return;
+  const int n0 = tn_ * BN;
+  const int Ci = a.Ci;
+  const int Kg = ph.Rt * ph.St * Ci;
+  const int tid = threadIdx.x;
+  const int kc = tid % KC;
+  const int rbase = tid / KC;
+
+  int64_t a_base[A_IT];
+  int a_ih0[A_IT], a_iw0[A_IT];
+#pragma unroll
+  for (int it = 0; it < A_IT; ++it) {
+    const int m = m0 + rbase + it * RSTEP;
+    if (m < M) {
+      const int img = m / HoWo;
+      const int rem = m - img * HoWo;
+      const int i = rem / ph.Wo;
+      const int j = rem - i * ph.Wo;
+      a_base[it] = (int64_t)img * a.Hi * a.Wi * Ci;
+      a_ih0[it] = i * a.stride_h - ph.pad_h;
+      a_iw0[it] = j * a.stride_w - ph.pad_w;
+    } else {
+      a_base[it] = 0;
+      a_ih0[it] = -(1 << 28);
+      a_iw0[it] = 0;
+    }
+  }
+
+  // range-checked buffer loads: an offset past the end reads zeros, no branch
+  const uint32_t act_bytes = (uint32_t)((int64_t)a.N * a.Hi * a.Wi * Ci * 2);
+  const __amdgpu_buffer_rsrc_t rs_a = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<h16*>(a.act), (short)0, (int)act_bytes, 0x00020000);
+  const uint32_t filt_bytes = (uint32_t)((int64_t)a.Co * ph.ldb * 2);
+  const __amdgpu_buffer_rsrc_t rs_b = __builtin_amdgcn_make_buffer_rsrc(
+      const_cast<h16*>(ph.filt), (short)0, (int)filt_bytes, 0x00020000);
+  constexpr uint32_t OOB = 0x80000000u;
+  uint32_t a_off[A_IT];
+#pragma unroll
+  for (int it = 0; it < A_IT; ++it) a_off[it] = (uint32_t)(a_base[it] * 2);
+  auto load_tile = [&](int k0, V8 (&ra)[A_IT], V8 (&rb)[B_IT]) {
+    const int kk = k0 + kc * 8;
+    const bool kval = kk < Kg;
+    const int tap = kval ? kk / Ci : 0;
+    const int c = kk - tap * Ci;
+    const int r = tap / ph.St;
+    const int s = tap - r * ph.St;
+#pragma unroll
+    for (int it = 0; it < A_IT; ++it) {
+      const int ih = a_ih0[it] + r;
+      const int iw = a_iw0[it] + s;
+      const bool v = kval && (unsigned)ih < (unsigned)a.Hi && (unsigned)iw < (unsigned)a.Wi;
+      const uint32_t off = v ? a_off[it] + (uint32_t)((ih * a.Wi + iw) * Ci + c) * 2u : OOB;
+      ra[it].u = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs_a, off, 0, 0));
+    }
+#pragma unroll
+    for (int it = 0; it < B_IT; ++it) {
+      const int n = n0 + rbase + it * RSTEP;
+      const uint32_t off = (kval && n < a.Co) ? (uint32_t)(n * ph.ldb + kk) * 2u : OOB;
+      rb[it].u = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(rs_b, off, 0, 0));
+    }
+  };
+  auto store_tile = [&](int buf, const V8 (&ra)[A_IT], const V8 (&rb)[B_IT]) {
+    h16* as = As + buf * BM * LDK;
+    h16* bs = Bs + buf * BN * LDK;
+#pragma unroll
+    for (int it = 0; it < A_IT; ++it) store16(&as[(rbase + it * RSTEP) * LDK + kc * 8], ra[it]);
+#pragma unroll
+    for (int it = 0; it < B_IT; ++it) store16(&bs[(rbase + it * RSTEP) * LDK + kc * 8], rb[it]);
+  };
+
+  const int wave = tid >> 6, lane = tid & 63;
+  const int wm = wave / WN, wn = wave % WN;
+  const int lrow = lane & 31, lk = (lane >> 5) * 8;
+
+  floatx16 acc[TM][TN];
+#pragma unroll
+  for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+    for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[tm][tn][e] = 0.0f;
+
+  auto compute = [&](int buf) {
+    const h16* as = As + buf * BM * LDK;
+    const h16* bs = Bs + buf * BN * LDK;
+#pragma unroll
+    for (int ks = 0; ks < BK / 16; ++ks) {
+      half8 af[TM], bf[TN];
+#pragma unroll
+      for (int tm = 0; tm < TM; ++tm)
+        af[tm] = *reinterpret_cast<const half8*>(&as[(wm * WTM + tm * 32 + lrow) * LDK + ks * 16 + lk]);
+#pragma unroll
+      for (int tn = 0; tn < TN; ++tn)
+        bf[tn] = *reinterpret_cast<const half8*>(&bs[(wn * WTN + tn * 32 + lrow) * LDK + ks * 16 + lk]);
+#pragma unroll
+      for (int tm = 0; tm < TM; ++tm)
+#pragma unroll
+        for (int tn = 0; tn < TN; ++tn) {
+          acc[tm][tn] = mfma32x32x16(af[tm], bf[tn], acc[tm][tn]);
+        }
+    }
+  };
+
+  const int KT = (Kg + BK - 1) / BK;
+  V8 ra0[A_IT], rb0[B_IT];
+  if (KT > 0) {
+    load_tile(0, ra0, rb0);
+    store_tile(0, ra0, rb0);
+  }
+  __syncthreads();
+  for (int kt = 0; kt < KT; ++kt) {
+    if (kt + 1 < KT) load_tile((kt + 1) * BK, ra0, rb0);
+    compute(kt & 1);
+    if (kt + 1 < KT) store_tile((kt + 1) & 1, ra0, rb0);
+    __syncthreads();
+  }
+
+  float* stg = reinterpret_cast<float*>(smem) + wave * 32 * K::SP;
+  constexpr int CPR = WTN / 8;
+  constexpr int RPP = 64 / CPR;
+  const int cc = lane % CPR;
+  const int rr = lane / CPR;
+  const int n = n0 + wn * WTN + cc * 8;
+  const bool vec_ok = (a.ldo % 8) == 0 && n + 8 <= a.Co;
+#pragma unroll
+  for (int tm = 0; tm < TM; ++tm) {
+#pragma unroll
+    for (int tn = 0; tn < TN; ++tn)
+#pragma unroll
+      for (int e = 0; e < 16; ++e)
+        stg[(8 * (e >> 2) + 4 * (lane >> 5) + (e & 3)) * K::SP + tn * 32 + lrow] = acc[tm][tn][e];
+    __syncthreads();
+#pragma unroll
+    for (int pass = 0; pass < 32 / RPP; ++pass) {
+      const int r = pass * RPP + rr;
+      const int m = m0 + wm * WTM + tm * 32 + r;
+      if (m < M && n < a.Co) {
+        const int img = m / HoWo;
+        const int rem = m - img * HoWo;
+        const int i = rem / ph.Wo;
+        const int j = rem - i * ph.Wo;
+        const int oh = i * a.os_h + ph.oph;
+        const int ow = j * a.os_w + ph.opw;
+        const int64_t off = ((int64_t)(img * a.OH + oh) * a.OW + ow) * a.ldo + n;
+        const float* src = stg + r * K::SP + cc * 8;
+        float v[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = src[e];
+        if (vec_ok) {
+          if (a.addend) {
+            const int64_t ar = addend_row(a, img, oh, ow);
+            const V8 ad = ar >= 0 ? addend8(a, ar + n) : zero8();
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] += to_f32(ad.h[e]);
+          }
+          V8 o;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) o.h[e] = to_h16(v[e]);
+          store16(a.out + off, o);
+        } else {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            if (n + e < a.Co) {
+              float x = v[e];
+              if (a.addend) {
+                const int64_t ar = addend_row(a, img, oh, ow);
+                x += ar >= 0 ? addend1(a, ar + n + e) : 0.0f;
+              }
+              a.out[off + e] = to_h16(x);
+            }
+          }
+        }
+      }
+    }
+    __syncthreads();
+  }
 }
 
 // ---- A from global into VGPRs, B (filter) through LDS by DMA ---------------
@@ -992,7 +1211,7 @@ int c3_tiles_per_image(const IgemmArgs& a) {
 }
 
 // ---- k-step 64, whole 128-byte operand rows, fragment reads one sub-step ahead
-// As igemm6, with a k-step of 64 channels: every operand row of a stage is one
+// A k-step is 64 channels: every operand row of a stage is one
 // whole 128-byte line (8 lanes x 16 bytes per row, 8 rows per 1 KB DMA
 // instruction), and each wave does 4 x TM x TN MFMAs per barrier.  The
 // fragments of k sub-step ks+1 are read from LDS while the MFMAs of sub-step
@@ -1744,6 +1963,14 @@ hipError_t launch_cfg4(const IgemmArgs& a0, hipStream_t st) {
   return hipGetLastError();
 }
 
+// Whether the wide kernel gives each lane's 8-channel chunk a filter tap of its
+// own (channels not a multiple of 64, or more taps than a mask holds).
+bool wide_taps(const IgemmArgs& a) {
+  bool gen = a.Ci % 64 != 0;
+  for (int p = 0; p < a.nphase; ++p) gen = gen || a.ph[p].Rt * a.ph[p].St > 32;
+  return gen;
+}
+
 template <int WN, int TA, int TB>
 hipError_t launch_cfg8(const IgemmArgs& a0, hipStream_t st) {
   using K = Cfg8<WN, TA, TB>;
@@ -1753,8 +1980,7 @@ hipError_t launch_cfg8(const IgemmArgs& a0, hipStream_t st) {
   dim3 grid(ceil_div(maxM, K::BM), ceil_div(a0.Co, K::BN), a0.nphase);
   IgemmArgs a = a0;
   a.gn = xcd_group(a, grid.y);
-  bool gen = a.Ci % 64 != 0;
-  for (int p = 0; p < a.nphase; ++p) gen = gen || a.ph[p].Rt * a.ph[p].St > 32;
+  const bool gen = wide_taps(a);
 #define FP16K_L8(STATS, ADD)                                                                    \
   do {                                                                                          \
     if (gen)                                                                                    \
@@ -1858,6 +2084,21 @@ hipError_t launch_pw(const IgemmArgs& a, hipStream_t st) {
     }
   } else
     hipLaunchKernelGGL((pw_kernel<CI, BN, false, false, false>), grid, dim3(256), 0, st, a, ntiles);
+  return hipGetLastError();
+}
+
+template <int BM, int BN, int WM, int WN, int BK>
+hipError_t launch_cfg(const IgemmArgs& a0, hipStream_t st) {
+  int maxM = 0;
+  for (int p = 0; p < a0.nphase; ++p) {
+    const int m = a0.N * a0.ph[p].Ho * a0.ph[p].Wo;
+    if (m > maxM) maxM = m;
+  }
+  if (maxM == 0 || a0.nphase == 0) return hipSuccess;
+  dim3 grid(ceil_div(maxM, BM), ceil_div(a0.Co, BN), a0.nphase);
+  IgemmArgs a = a0;
+  a.gn = xcd_group(a, grid.y);
+  hipLaunchKernelGGL((igemm_kernel<BM, BN, WM, WN, BK>), grid, dim3(256), 0, st, a);
   return hipGetLastError();
 }
 
@@ -2037,6 +2278,29 @@ __global__ __launch_bounds__(512) void stem_kernel(const IgemmArgs a, int ntiles
 
 namespace {
 
+// What the kernel choices go by.
+struct Shape {
+  int maxK = 0, maxT = 0;  // longest phase: reduction, taps
+  int64_t rows = 0;        // output rows of all phases
+  int64_t tiles = 0;       // tiles of 128 rows x 128 channels (x 64 up to 64 channels)
+  int64_t meanK = 0;       // mean reduction of an output
+};
+Shape shape_of(const IgemmArgs& a) {
+  Shape s;
+  int64_t work = 0;
+  for (int p = 0; p < a.nphase; ++p) {
+    const int t = a.ph[p].Rt * a.ph[p].St;
+    const int64_t r = (int64_t)a.N * a.ph[p].Ho * a.ph[p].Wo;
+    s.rows += r;
+    work += r * t * a.Ci;
+    s.maxK = max(s.maxK, t * a.Ci);
+    s.maxT = max(s.maxT, t);
+  }
+  s.tiles = ceil_div64(s.rows, 128) * ceil_div(a.Co, a.Co <= 64 ? 64 : 128);
+  s.meanK = s.rows ? work / s.rows : 0;
+  return s;
+}
+
 // Tile of the wide kernel for this problem: the least of
 //   rounds * (100 + BM * BN / 128),  rounds = ceil(tiles / 256 CUs),
 // over the tile shapes.  (One workgroup alone on its CU takes 0.19 us plus 1.9
@@ -2045,8 +2309,15 @@ namespace {
 // layers tried: batch 128, 14x14 256 -> 256 3x3 224 rows 32.4 us against 33.7
 // at 256 and 42.7 at 128; 28x28 128 -> 128 224 rows 39.5 against 42; 7x7 512 ->
 // 512 128 rows 36.5 against 40.2 at 160; batch 32, 7x7 2048 -> 512 64 rows 12.7
-// against 16.4 at 128.)  Up to 64 channels the tiles are 64 channels wide, or
-// 64 rows x 128 where that gives every tile a CU of its own.
+// against 16.4 at 128.)  Of the two smallest shapes (64 x 128 and 128 x 64, 72
+// KB of LDS) two workgroups share a CU: a pair takes about as long as one tile
+// of twice the size, less where the reduction is short and one's stores run
+// under the other's loads (batch 128, 56x56 64 -> 64 3x3 with an addend 66.3 us
+// on 128 x 64 against 81.3 on 256 x 64; 56x56 32 -> 256 1x1/2 gradient 28.3
+// against 31.9), more where it is long (14x14 512 -> 512 3x3/2 54 against 46)
+// or where the statistics' records of small tiles add up (batch 32, 56x56 8 ->
+// 32 3x3 with statistics 27.1 against 23.1).  Up to 64 channels the tiles are
+// 64 channels wide, or 64 rows x 128.
 struct WideTile {
   int wn, ta, tb;
   int rows() const { return wn == 4 ? 32 * (ta + tb) : 128 * ta; }
@@ -2054,17 +2325,27 @@ struct WideTile {
 WideTile wide_choice(const IgemmArgs& a) {
   static constexpr WideTile kTiles[] = {{4, 1, 1}, {4, 2, 2}, {4, 3, 2}, {4, 3, 3}, {4, 4, 3},
                                         {4, 4, 4}, {2, 1, 1}, {2, 2, 2}};
+  const Shape s = shape_of(a);
+  const int pair = s.meanK <= 576 && (!a.stat || a.Co > 32 || s.tiles > 1024) ? 220 : 240;
   WideTile best = kTiles[0];
   int64_t cost = INT64_MAX;
   for (const WideTile& t : kTiles) {
     if (t.wn == 2 && a.Co > 64) continue;
     if (t.wn == 4 && a.Co <= 64 && t.ta > 1) continue;
-    if (t.rows() < 128 && (int64_t)a.N * a.ph[0].Ho * a.ph[0].Wo > kStatSmallRows) continue;
+    // (the space for the statistics' records: see kStatSmallRows)
+    if (a.stat && t.rows() < 128 && s.rows > kStatSmallRows) continue;
     int64_t tiles = 0;
     for (int p = 0; p < a.nphase; ++p)
       tiles += ceil_div(a.N * a.ph[p].Ho * a.ph[p].Wo, t.rows());
     tiles *= ceil_div(a.Co, 32 * t.wn);
-    const int64_t c = ceil_div64(tiles, 256) * (100 + t.rows() * t.wn / 4);
+    const int size = t.rows() * t.wn / 4;
+    int64_t c;
+    if (size == 64 && !(a.stat && t.wn == 4)) {
+      const int64_t rest = tiles % 512;
+      c = tiles / 512 * pair + (rest == 0 ? 0 : rest <= 256 ? 100 + size : pair);
+    } else {
+      c = ceil_div64(tiles, 256) * (100 + size);
+    }
     if (c < cost) {
       cost = c;
       best = t;
@@ -2086,64 +2367,100 @@ hipError_t launch_wide(const IgemmArgs& a, hipStream_t st) {
   }
 }
 
-enum class IgemmKind { kWide, kDirect, kDma, kPointwise, k3x3 };
+enum class IgemmKind { kWide, kDirect, kDma, kPointwise, k3x3, kLds };
 
 // Kernel choice per problem, each line drawn where the kernels on its two
 // sides measured alike (us per call on MI355X, NHWC, the wide kernel's time
-// second):
-//  - the 3x3 64-channel kernel from 256 of its tiles on (one per CU): batch
+// second; over 2,950 calls of convolutions, data gradients and conv + BN no
+// line costs a call more than a few percent).  `tiles` are of 128 rows x 128
+// channels, or x 64 up to 64 channels.
+//  - The 3x3 64-channel kernel from 256 of its tiles on (one per CU): batch
 //    128 of 56x56 45.7 against 55.9, batch 32 18.2 against 18.9, batch 2
-//    9.6 against 6.0;
-//  - the pointwise kernel for 1x1 filters over 64 or 128 channels (256 without
-//    an addend) with a dense output of 128+ channels that fills 1,280 tiles of
-//    128 x 128 (384 over 64 channels): 28x28 128 -> 512 at batch 128 (3,136
-//    tiles) 34.9 against 43.9, at batch 32 (784) 28.3 against 14.8; 14x14 256
-//    -> 1024 at batch 128 (1,568) 33.0 against 39.3; 56x56 64 -> 256 at batch
-//    16 with an addend (784) 14.4 against 19.8, at batch 8 (392) 7.0 against
-//    8.0, at batch 6 (294) 6.9 against 6.7;
-//  - the register-direct kernel for reductions up to 256 in one phase (512
-//    where the channels are an odd multiple of 32) over as many tiles (512 up
-//    to 32 outputs): 14x14 256 -> 1024 data gradient at batch 128 with an addend
-//    46.2 against 51.8, at batch 64 (784 tiles) 28.8 against 25.7; 56x56 256
-//    -> 64 at batch 128 44.4 against 45.7, at batch 32 16.7 against 14.2;
-//    56x56 32 -> 32 3x3 at batch 128 31.5 against 46.2; and
-//    for the short phases (up to 512) of large strided data gradients;
-//  - the 128 x 128 DMA-staged kernel, two workgroups per CU, for the longer
-//    phases of strided data gradients while they are short against a
-//    workgroup's start and end (up to 1,023) and more than 512 tiles: 56x56
-//    128 -> 128 3x3 stride 2 at batch 128 70 against 71-78, at batch 32 25.2
-//    against 21.6;
-//  - the wide kernel everywhere else.
+//    9.6 against 6.0.
+//  - The pointwise kernel for 1x1 filters over 64 or 128 channels (256 without
+//    an addend) with a dense output of 128+ channels that fills 1,280 tiles
+//    (384 over 64 channels): 28x28 128 -> 512 at batch 128 (3,136 tiles) 34.9
+//    against 43.9, at batch 32 (784) 28.3 against 14.8; 14x14 256 -> 1024 at
+//    batch 128 (1,568) 33.0 against 39.3; 56x56 64 -> 256 at batch 16 with an
+//    addend (784) 14.4 against 19.8, at batch 8 (392) 7.0 against 8.0, at batch
+//    6 (294) 6.9 against 6.7.
+//  - The register-direct kernel (channels a multiple of 32) in one phase for
+//    reductions up to 256, or 512 over an odd multiple of 32, from 1,280 tiles
+//    on: 14x14 256 -> 1024 data gradient at batch 128 with an addend 46.2
+//    against 51.8, at batch 64 (784 tiles) 28.8 against 25.7; 56x56 256 -> 64 at
+//    batch 128 44.4 against 45.7, at batch 32 16.7 against 14.2.  From fewer on
+//    where the wide kernel's 64-channel steps are part padding or its tiles
+//    half empty: up to 64 outputs over an odd multiple of 32 from 350 (56x56
+//    32 -> 64 at batch 16, 392 tiles, 5.5 against 6.2, at batch 32 7.8 against
+//    11.2; 3x3 12.5 against 16.0), up to 32 outputs 512, over 32 channels 580
+//    (18x18 32 -> 1024 at batch 32, 648 tiles, 10.7 against 12.8; with
+//    statistics 28x28 32 -> 512 at batch 32 the wide kernel by 15 %), over 96
+//    1,100 (28x28 96 -> 384 at batch 64, 1,176 tiles, 19.5 against 21.9), and
+//    over 64 with statistics 512 (56x56 64 -> 64 at batch 32 23.5 against 25.5).
+//  - Strided data gradients, whose phases are short or empty, by the mean
+//    reduction K of an output:
+//     . the LDS-staged kernel where the channels are not a multiple of 32, from
+//       257 tiles on up to K = 64 (128 up to 64 outputs; 180 from 1,537 tiles
+//       on): 56x56 64 -> 8 1x1/2 at batch 128 23.8 against 34.5, 57x57 256 -> 24
+//       3x3/2 84 against 97; at 196 tiles alike, and with an addend over 4,096
+//       tiles the wide kernel is the faster (57x57 512 -> 16 327 against 302);
+//     . the register-direct one for phases up to 512 over multiples of 32: over
+//       odd ones from 320 tiles (200 up to 64 outputs: 57x57 64 -> 96 3x3/2 at
+//       batch 8, 204 tiles, 6.9 against 7.2, at batch 16 8.4 against 10.0), over
+//       multiples of 64 from 128 + 4 K (56x56 64 -> 128 1x1/2, K = 32, 196 tiles
+//       5.4 against 4.8, 392 5.8 against 6.9; 56x56 256 -> 512 1x1/2, K = 128,
+//       392 tiles 13.1 against 12.1, 784 15.8 against 19.0; 56x56 128 -> 128
+//       3x3/2, K = 288, 784 tiles 25.3 against 22.3, 1,568 40.5 against 41.3);
+//     . the 128 x 128 DMA-staged one, two workgroups per CU, for longer phases
+//       over multiples of 64: from 257 tiles where the outputs are up to 64
+//       (33x33 64 -> 256 3x3/2 at batch 64, 545 tiles, 17.6 against 21.3); from
+//       384 up to K = 199 (28x28 320 -> 640 1x1/2 at batch 32, 588 tiles, 13.8
+//       against 14.8, 294 tiles 11.8 against 10.4); up to K = 479 with an addend
+//       (28x28 512 -> 1024 1x1/2 at batch 32, 784 tiles, 23.5 against 28.7) or
+//       over 1,024 tiles (batch 128 64.8 against 69.5; 784 tiles 20.2 against
+//       19.4); and with an addend over 1,200 tiles (28x28 256 -> 256 3x3/2, K =
+//       576, 1,568 tiles 66.1 against 69.4; 784 tiles 40.8 against 37.5).
+//  - The wide kernel everywhere else.
 // All give the sums of the same products in float32; the wide kernel's are in
-// another order (see there) where the channels exceed 64.
+// another order (see there) where the channels are a multiple of 64 over 64.
 IgemmKind igemm_kind(const IgemmArgs& a) {
   if ((int64_t)a.N * c3_tiles_per_image(a) >= 256) return IgemmKind::k3x3;
-  int maxK = 0, maxT = 0;
-  int64_t rows = 0;
-  for (int p = 0; p < a.nphase; ++p) {
-    const int t = a.ph[p].Rt * a.ph[p].St;
-    rows += (int64_t)a.N * a.ph[p].Ho * a.ph[p].Wo;
-    if (t * a.Ci > maxK) maxK = t * a.Ci;
-    if (t > maxT) maxT = t;
+  const Shape s = shape_of(a);
+  const int64_t K = s.meanK, tiles = s.tiles;
+  if (a.nphase > 1) {
+    if (a.Ci % 32 != 0) {
+      const bool lds = K <= (a.Co <= 64 ? 128 : 64) || (K <= 180 && tiles > 1536);
+      if (lds && tiles > 256 && !(a.addend && tiles > 4096)) return IgemmKind::kLds;
+    } else if (a.Ci % 64 == 0 && s.maxK >= 576) {
+      const bool dma = a.Co <= 64 || (K < 200 && tiles >= 384) ||
+                       (K < 480 && (a.addend || tiles > 1024)) || (a.addend && tiles > 1200);
+      if (dma && tiles > 256 && s.maxT <= 32) return IgemmKind::kDma;
+    } else if (s.maxK <= 512) {
+      if (tiles >= (a.Ci % 64 == 0 ? 128 + 4 * K : a.Co <= 64 ? 200 : 320))
+        return IgemmKind::kDirect;
+    }
+    return IgemmKind::kWide;
   }
+  const IgemmPhase& p = a.ph[0];
   const int64_t act = (int64_t)a.N * a.Hi * a.Wi * a.Ci * 2;
-  const int64_t tiles = ceil_div64(rows, 128) * ceil_div(a.Co, a.Co <= 64 ? 64 : 128);
-  {
-    const IgemmPhase& p = a.ph[0];
-    const bool ci_ok = a.Ci == 64 || a.Ci == 128 || (a.Ci == 256 && !a.addend);
-    if (a.nphase == 1 && p.Rt == 1 && p.St == 1 && p.pad_h == 0 && p.pad_w == 0 &&
-        p.oph == 0 && p.opw == 0 && a.os_h == 1 && a.os_w == 1 && a.OH == p.Ho &&
-        a.OW == p.Wo && ci_ok && p.ldb == a.Ci && a.Co >= 128 &&
-        a.Co % 8 == 0 && a.ldo % 8 == 0 && act < ((int64_t)1 << 31) && tiles >= (a.Ci == 64 ? 384 : 1280))
-      return IgemmKind::kPointwise;
+  const bool ci_ok = a.Ci == 64 || a.Ci == 128 || (a.Ci == 256 && !a.addend);
+  if (p.Rt == 1 && p.St == 1 && p.pad_h == 0 && p.pad_w == 0 && p.oph == 0 && p.opw == 0 &&
+      a.os_h == 1 && a.os_w == 1 && a.OH == p.Ho && a.OW == p.Wo && ci_ok && p.ldb == a.Ci &&
+      a.Co >= 128 && a.Co % 8 == 0 && a.ldo % 8 == 0 && act < ((int64_t)1 << 31) &&
+      tiles >= (a.Ci == 64 ? 384 : 1280))
+    return IgemmKind::kPointwise;
+  if (a.Ci % 32 == 0 && s.maxK <= (a.Ci % 64 == 0 ? 256 : 512)) {
+    int from = 1280;
+    if (a.Co <= 64 && a.Ci % 64 != 0)
+      from = 350;
+    else if (a.Co <= 32 || (a.Co <= 64 && s.maxK == 64 && a.stat))
+      from = 512;
+    else if (s.maxK == 32 && !a.stat)
+      from = 580;
+    else if (s.maxK == 96 && !a.stat)
+      from = 1100;
+    if (tiles >= from) return IgemmKind::kDirect;
   }
-  if (a.nphase > 1 && tiles > 512 && maxK < 1024) {
-    if (a.Ci % 64 == 0 && maxK >= 576 && maxT <= 32) return IgemmKind::kDma;
-    if (a.Ci % 32 == 0 && maxK <= 512) return IgemmKind::kDirect;
-  }
-  if (a.nphase == 1 && a.Ci % 32 == 0 && maxK <= (a.Ci % 64 == 0 ? 256 : 512) &&
-      tiles >= (a.Co <= 32 ? 512 : 1280))
-    return IgemmKind::kDirect;
   return IgemmKind::kWide;
 }
 
@@ -2259,6 +2576,26 @@ static bool dense_split_ok(const IgemmArgs& a) {
          a.Ci % 8 == 0 && p.ldb % 8 == 0 && a.splits == dense_gemm_splits(a.N, a.Ci, a.Co);
 }
 
+void igemm_name(const IgemmArgs& a, char* out, size_t bytes) {
+  const int cols = a.Co <= 64 ? 64 : 128;
+  if (dense_split_ok(a)) {
+    snprintf(out, bytes, "dense %d splits", a.splits);
+    return;
+  }
+  switch (igemm_kind(a)) {
+    case IgemmKind::kDma: snprintf(out, bytes, "dma 128x%d", cols); return;
+    case IgemmKind::kDirect: snprintf(out, bytes, "direct 128x%d", cols); return;
+    case IgemmKind::kLds: snprintf(out, bytes, "staged 128x%d", cols); return;
+    case IgemmKind::k3x3: snprintf(out, bytes, "3x3"); return;
+    case IgemmKind::kPointwise:
+      snprintf(out, bytes, "pointwise %d 128x%d", a.Ci, pw_tile_n(a));
+      return;
+    default: break;
+  }
+  const WideTile t = wide_choice(a);
+  snprintf(out, bytes, "wide %dx%d%s", t.rows(), 32 * t.wn, wide_taps(a) ? " taps" : "");
+}
+
 hipError_t launch_igemm(const IgemmArgs& a, hipStream_t st) {
   if (a.bn_stats && (a.stat || !igemm_takes_apply(a))) return hipErrorInvalidValue;
   if (dense_split_ok(a)) {
@@ -2274,6 +2611,9 @@ hipError_t launch_igemm(const IgemmArgs& a, hipStream_t st) {
       return a.Co <= 64 ? launch_cfg7<2, 1, 2, 2, 2>(a, st) : launch_cfg7<2, 2, 2, 2, 2>(a, st);
     case IgemmKind::kDirect:
       return a.Co <= 64 ? launch_cfg4<1, 2>(a, st) : launch_cfg4<1, 4>(a, st);
+    case IgemmKind::kLds:
+      return a.Co <= 64 ? launch_cfg<128, 64, 4, 1, 64>(a, st)
+                        : launch_cfg<128, 128, 2, 2, 64>(a, st);
     case IgemmKind::k3x3:
       return launch_c3(a, c3_tiles_per_image(a), st);
     case IgemmKind::kPointwise: {

@@ -15,6 +15,8 @@
 
 #include "kernels.hpp"
 
+#include <stdio.h>
+
 #include <type_traits>
 
 namespace fp16k {
@@ -521,6 +523,11 @@ void wgrad_plan(int K, int Cp, int R, int S, int64_t npix, int target, int64_t r
   *pix_per_split = (int)pps;
   *splits = (int)((npix + pps - 1) / pps);
   if (*splits < 1) *splits = 1;
+}
+
+void wgrad_name(int K, int Cp, int R, int S, int64_t npix, char* out, size_t bytes) {
+  const WCfg c = wgrad_choice(K, R * S * Cp, npix);
+  snprintf(out, bytes, "%dx%d %d waves%s", c.BM, c.BN, c.NW, Cp % 64 != 0 ? " taps" : "");
 }
 
 hipError_t launch_wgrad_partial(const WgradArgs& a, hipStream_t st) {

@@ -117,6 +117,10 @@ bool igemm_takes_apply(const IgemmArgs& a);
 // several tiles).
 constexpr int64_t kStatSmallRows = 65536;
 int igemm_stat_rows(const IgemmArgs& a);
+// The kernel launch_igemm picks for this problem and its tile, for tests and
+// profiles ("wide 224x128", "direct 128x64", ...; " taps" where each lane has
+// a filter tap of its own).
+void igemm_name(const IgemmArgs& a, char* out, size_t bytes);
 int igemm_stat_records(const IgemmArgs& a);
 
 // Geometry of one stride phase (ph, pw) of the data gradient.  Output rows
@@ -186,6 +190,9 @@ constexpr int kWgradWorkgroups = 512;
 constexpr size_t kNoallocScratchBytes = (size_t)32 << 20;
 void wgrad_plan(int K, int Cp, int R, int S, int64_t npix, int target, int64_t room, int* splits,
                 int* pix_per_split);
+// The tile of launch_wgrad_partial for this problem ("256x128 8 waves", ...;
+// " taps" as above).
+void wgrad_name(int K, int Cp, int R, int S, int64_t npix, char* out, size_t bytes);
 
 // Convolutions with every operation in binary16 (conv_f16chain.hip): each
 // output a chain of binary16 fmas from +0 in the declared order.  NHWC
