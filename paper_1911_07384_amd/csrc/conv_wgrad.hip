@@ -453,6 +453,8 @@ struct WCfg {
 // 64 x 256 tiles left a quarter of the third empty: conv2_x 60.4 -> 53.5 us).
 inline WCfg wgrad_choice(int K, int Nw, int64_t npix) {
   if (K > 64 && Nw > 64) {
+    // a few k-steps of many tiles: writing the partial sums, two workgroups per CU
+    if (npix <= 8 * BKP && ceil_div(K, 128) * ceil_div(Nw, 128) > 256) return {128, 64, 3};
     static constexpr int kShapes[3][2] = {{128, 128}, {256, 128}, {128, 256}};
     WCfg best{128, 128, 3, 8};
     double cost = 1e30;
@@ -513,13 +515,24 @@ void wgrad_plan(int K, int Cp, int R, int S, int64_t npix, int target, int64_t r
   // than the slots cost a round (14x14: 576 workgroups for 512 slots)
   if ((cfg.NW == 8 || R * S == 1) && target > 256) target = 256;
   int64_t want = target / tiles;
-  const int64_t max_splits = (npix + 4 * BKP - 1) / (4 * BKP);  // four k-steps each or more
+  const int64_t steps = ceil_div64(npix, BKP);
+  // k-steps of a split: four or more, or two where that leaves most CUs idle
+  int64_t max_splits = ceil_div64(steps, 4);
+  if (max_splits * tiles < 64) max_splits = min(ceil_div64(steps, 2), ceil_div64(64, tiles));
   if (want > max_splits) want = max_splits;
+  // eight or more on the eight-wave kernel if it still fills half the CUs
+  const int64_t half = 128 / tiles;
+  if (cfg.NW == 8 && want > half && want * 8 > steps) want = max(half, steps / 8);
   if (want < 1) want = 1;
   auto per_split = [&](int64_t n) { return ceil_div64(ceil_div64(npix, n), BKP) * BKP; };
   int64_t pps = per_split(want);
   const int64_t n = ceil_div64(npix, pps);
-  if (n > room && 2 * room >= n && room >= 1) pps = per_split(room);
+  if (n > room && room >= 1) {
+    const int64_t t4 = K >= 128 ? (int64_t)ceil_div(K, 128) * ceil_div(Nw, 64)
+                                : (int64_t)ceil_div(K, 64) * ceil_div(Nw, Nw >= 128 ? 128 : 64);
+    const int64_t w4 = min(ceil_div64(kWgradWorkgroups, t4), ceil_div64(npix, 2 * BKP));
+    if (ceil_div64(npix, per_split(w4)) <= room) pps = per_split(room);
+  }
   *pix_per_split = (int)pps;
   *splits = (int)((npix + pps - 1) / pps);
   if (*splits < 1) *splits = 1;

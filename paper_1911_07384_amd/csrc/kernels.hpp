@@ -182,10 +182,11 @@ hipError_t launch_s2d3(const h16* src, h16* dst, int N, int H, int W, hipStream_
 hipError_t launch_wgrad_reduce_s2d3(float* partial, int splits, int K, h16* dw, hipStream_t st);
 // Split-K plan of the weight gradient: at most `target` workgroups (tiles x
 // splits; kWgradWorkgroups unless the caller asks for fewer, and 256 where one
-// per CU is the faster), each split at least four k-steps of pixels.  room:
-// the splits whose partial sums fit the array of fp16_conv_wgrad_noalloc beside
-// the staged operands; a plan of up to twice as many takes that many, so that
-// the call, which runs the same plan, does not lose the problem.
+// per CU is the faster), each split some k-steps of pixels.  room: the splits
+// whose partial sums fit the array of fp16_conv_wgrad_noalloc beside the staged
+// operands; a larger plan is cut to that many where 512 workgroups of four-wave
+// tiles would fit, so that the call, which runs the same plan, takes every
+// problem that such a plan fits.
 constexpr int kWgradWorkgroups = 512;
 constexpr size_t kNoallocScratchBytes = (size_t)32 << 20;
 void wgrad_plan(int K, int Cp, int R, int S, int64_t npix, int target, int64_t room, int* splits,
