@@ -1168,11 +1168,12 @@ __global__ __launch_bounds__(kT) void bn_apply_maxpool_vec(const h16* __restrict
   }
 }
 
-unsigned apply_grid(int64_t nthreads_wanted, int CV) {
+// (Any grid keeps a thread of the vectorised applies on one channel chunk: their
+// runs are multiples of TV, whole rows of C/8 chunks.)
+unsigned apply_grid(int64_t nthreads_wanted) {
   int64_t b = (nthreads_wanted + kT - 1) / kT;
   if (b > 16384) b = 16384;
   if (b < 1) b = 1;
-  (void)CV;  // kT is a multiple of CV, so any grid keeps each thread on one chunk
   return (unsigned)b;
 }
 
@@ -1197,7 +1198,7 @@ int bwd_mode(const BnArgs& a, const h16* y, const h16* res, const h16* dres, boo
 hipError_t launch_fwd_apply_vec(int mode, const Plan& p, const Geo& g, const h16* x,
                                 const h16* gamma, const h16* beta, const h16* res, h16* y,
                                 const float* stats, float s, uint8_t* mout, hipStream_t st) {
-  const dim3 grid(apply_grid(g.M * p.CV / kApplyU, p.CV));
+  const dim3 grid(apply_grid(g.M * p.CV / kApplyU));
   switch (mode) {
 #define FP16K_CASE(m)                                                                          \
   case m:                                                                                      \
@@ -1283,7 +1284,7 @@ hipError_t launch_bn_fwd(const BnArgs& a, const h16* x, const h16* gamma, const 
   if (!use_stats) bn_fwd_stats(a, p, g, x, stats, ws, st);
   if (p.nchw) {
     const int PC = nchw_chunks(a), items = a.N * a.C * PC;
-    const dim3 grid(apply_grid(items, 1));
+    const dim3 grid(apply_grid(items));
     if (res)
       hipLaunchKernelGGL(bn_fwd_apply_nchw<true>, grid, dim3(kT), 0, st, x, gamma, beta, res, y,
                          stats, g, PC, items, a.post_scale, a.relu);
@@ -1296,7 +1297,7 @@ hipError_t launch_bn_fwd(const BnArgs& a, const h16* x, const h16* gamma, const 
                              a.post_scale, mout, st);
     if (e != hipSuccess) return e;
   } else {
-    hipLaunchKernelGGL(bn_fwd_apply_gen, dim3(apply_grid(g.M * a.C / 4, 1)), dim3(kT), 0, st, x,
+    hipLaunchKernelGGL(bn_fwd_apply_gen, dim3(apply_grid(g.M * a.C / 4)), dim3(kT), 0, st, x,
                        gamma, beta, res, y, stats, g, a.post_scale, a.relu);
   }
   return hipGetLastError();
@@ -1314,7 +1315,7 @@ hipError_t launch_bn_fwd_maxpool(const BnArgs& a, const PoolArgs& pa, const h16*
   const Geo g = make_geo(a);
   if (!use_stats) bn_fwd_stats(a, p, g, x, stats, ws, st);
   const int64_t total = (int64_t)pa.N * pa.P * pa.Q * (pa.C / 8);
-  hipLaunchKernelGGL((bn_apply_maxpool_vec<3, 3>), dim3(apply_grid(total, p.CV)), dim3(kT), 0, st,
+  hipLaunchKernelGGL((bn_apply_maxpool_vec<3, 3>), dim3(apply_grid(total)), dim3(kT), 0, st,
                      x, gamma, beta, stats, a.post_scale, pa, y, idx);
   return hipGetLastError();
 }
@@ -1354,7 +1355,7 @@ hipError_t launch_bn_fwd_bands(const BnArgs& a, const float* part, int nb, int r
                              a.post_scale, mout, st);
     if (e != hipSuccess) return e;
   } else {
-    hipLaunchKernelGGL(bn_fwd_apply_gen, dim3(apply_grid(g.M * a.C / 4, 1)), dim3(kT), 0, st, x,
+    hipLaunchKernelGGL(bn_fwd_apply_gen, dim3(apply_grid(g.M * a.C / 4)), dim3(kT), 0, st, x,
                        gamma, beta, res, y, stats, g, a.post_scale, a.relu);
   }
   return hipGetLastError();
@@ -1422,11 +1423,11 @@ hipError_t launch_bn_bwd(const BnArgs& a, const h16* x, const h16* y, const h16*
                        p.G, part, gamma, stats, dgamma, dbeta, coef);
   if (p.nchw) {
     const int items = a.N * a.C * PC;
-    FP16K_NCHW(bn_bwd_apply_nchw, dim3(apply_grid(items, 1)), coef, g, PC, items, a.post_scale,
+    FP16K_NCHW(bn_bwd_apply_nchw, dim3(apply_grid(items)), coef, g, PC, items, a.post_scale,
                a.relu, dx, dres);
 #undef FP16K_NCHW
   } else if (p.vec) {
-    const dim3 grid(apply_grid(g.M * p.CV / (kApplyU / 2), p.CV));
+    const dim3 grid(apply_grid(g.M * p.CV / (kApplyU / 2)));
     switch (mode) {
 #define FP16K_CASE(m)                                                                          \
   case m:                                                                                      \
@@ -1439,7 +1440,7 @@ hipError_t launch_bn_bwd(const BnArgs& a, const h16* x, const h16* y, const h16*
         return hipErrorInvalidValue;
     }
   } else {
-    hipLaunchKernelGGL(bn_bwd_apply_gen, dim3(apply_grid(g.M * a.C / 4, 1)), dim3(kT), 0, st, x,
+    hipLaunchKernelGGL(bn_bwd_apply_gen, dim3(apply_grid(g.M * a.C / 4)), dim3(kT), 0, st, x,
                        y, dy, gamma, beta, res, stats, coef, g, a.post_scale, a.relu, dx, dres);
   }
   return hipGetLastError();

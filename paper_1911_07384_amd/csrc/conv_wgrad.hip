@@ -439,10 +439,10 @@ struct WCfg {
 };
 // From 65 output channels and 65 filter columns on: eight waves, one workgroup
 // per CU, the tile of the least
-//   rounds * k-steps of a split * area + splits * K * Nw * 1/8
+//   rounds * k-steps of a split * area * 0.62 + splits * K * Nw * 8 / 4e6  (us)
 // among 128 x 128 and, where those come in a count that divides 256 badly,
-// 256 x 128 and 128 x 256 (splits = 256 / tiles; the units are one 128 x 128
-// k-step of 0.62 us at full load and the 8 bytes each partial sum moves).
+// 256 x 128 and 128 x 256 (area 2), with 256 / tiles splits: a 128 x 128 k-step
+// takes 0.62 us at full load, and each partial sum moves 8 bytes at 4 TB/s.
 // Measured with the reduction, batch 128: 14x14 256 -> 256 3x3 55.5 -> 42.0 us
 // (four waves on 128 x 64, two workgroups per CU, 576 of them for 512 slots),
 // 28x28 128 -> 128 47.3 -> 42.3, 7x7 512 -> 512 53.4 -> 41.7 (256 x 128; 54 on
@@ -453,7 +453,8 @@ struct WCfg {
 // 64 x 256 tiles left a quarter of the third empty: conv2_x 60.4 -> 53.5 us).
 inline WCfg wgrad_choice(int K, int Nw, int64_t npix) {
   if (K > 64 && Nw > 64) {
-    // a few k-steps of many tiles: writing the partial sums, two workgroups per CU
+    // a few k-steps of many tiles are the writing of partial sums, better by two
+    // workgroups per CU (432 pixels, 1024 x 4608: 26.9 -> 24.2 us)
     if (npix <= 8 * BKP && ceil_div(K, 128) * ceil_div(Nw, 128) > 256) return {128, 64, 3};
     static constexpr int kShapes[3][2] = {{128, 128}, {256, 128}, {128, 256}};
     WCfg best{128, 128, 3, 8};
@@ -517,10 +518,14 @@ void wgrad_plan(int K, int Cp, int R, int S, int64_t npix, int target, int64_t r
   int64_t want = target / tiles;
   const int64_t steps = ceil_div64(npix, BKP);
   // k-steps of a split: four or more, or two where that leaves most CUs idle
+  // (9 steps, 256 x 176: 8.2 -> 7.4 us)
   int64_t max_splits = ceil_div64(steps, 4);
   if (max_splits * tiles < 64) max_splits = min(ceil_div64(steps, 2), ceil_div64(64, tiles));
   if (want > max_splits) want = max_splits;
-  // eight or more on the eight-wave kernel if it still fills half the CUs
+  // eight or more on the eight-wave kernel if that still fills half the CUs: fewer
+  // partial sums (14x14 256 -> 1024 1x1 at batch 32, 6 steps a split on 16 splits
+  // 21.6 us, 12 steps on 8 splits 18.3; 3x3 128 -> 128 over 6,272 pixels 17.0 and
+  // 15.0; with 12 steps a split and more the longer ones lose)
   const int64_t half = 128 / tiles;
   if (cfg.NW == 8 && want > half && want * 8 > steps) want = max(half, steps / 8);
   if (want < 1) want = 1;

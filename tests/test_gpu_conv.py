@@ -19,7 +19,9 @@ pytestmark = pytest.mark.gpu
 
 PASSES = ("fwd", "dgrad", "wgrad")
 
-# (n, c, h, w, k, r, s, stride, pad, layout)
+# (n, c, h, w, k, r, s, stride, pad, layout): small problems, which but for the
+# stem and the classifier run on the wide kernel's smaller tiles; the kernels
+# that larger ones take are in test_gpu_kernel_edges.py
 SHAPES = [
     (2, 64, 56, 56, 64, 3, 3, 1, 1, "NHWC"),    # the single 3x3 layer, N = 2 (full size)
     (2, 64, 28, 28, 64, 3, 3, 1, 1, "NHWC"),    # several M tiles and a ragged last tile
@@ -44,23 +46,23 @@ SHAPES = [
     (2, 64, 12, 12, 64, 3, 3, 1, 1, "NCHW"),
     (2, 3, 20, 20, 16, 7, 7, 2, 3, "NCHW"),
     (2, 64, 15, 15, 128, 1, 1, 2, 0, "NCHW"),
-    (2, 64, 15, 15, 64, 3, 3, 2, 1, "NHWC"),    # strided 3x3 on the DMA-staged kernel (fwd)
-    (2, 256, 9, 9, 192, 3, 3, 2, 1, "NHWC"),    # dgrad phases of up to 4 taps x 192: DMA-staged; ragged N
-    (2, 1024, 5, 5, 96, 1, 1, 1, 0, "NHWC"),    # 1x1 with a 1024-long reduction: DMA-staged
-    (2, 512, 7, 7, 128, 1, 1, 1, 0, "NHWC"),    # 1x1 with a 512-long reduction: DMA-staged fwd
-    (2, 128, 7, 9, 512, 1, 1, 1, 0, "NHWC"),    # ... and DMA-staged data gradient
+    (2, 64, 15, 15, 64, 3, 3, 2, 1, "NHWC"),    # strided 3x3 over 64 channels
+    (2, 256, 9, 9, 192, 3, 3, 2, 1, "NHWC"),    # dgrad phases of up to 4 taps x 192
+    (2, 1024, 5, 5, 96, 1, 1, 1, 0, "NHWC"),    # 1x1 with a 1024-long reduction
+    (2, 512, 7, 7, 128, 1, 1, 1, 0, "NHWC"),    # 1x1 with a 512-long reduction
+    (2, 128, 7, 9, 512, 1, 1, 1, 0, "NHWC"),    # ... in the data gradient
     (2, 24, 9, 9, 64, 3, 3, 1, 1, "NHWC"),      # wgrad: 8-channel chunks of one 64-column block span taps
     (2, 8, 12, 12, 128, 1, 1, 2, 0, "NHWC"),    # wgrad: 8 channels, K = 128
-    (2, 64, 20, 20, 192, 1, 1, 1, 0, "NHWC"),   # pointwise fwd: 64 -> 192, second channel tile partial
-    (3, 128, 9, 9, 384, 1, 1, 1, 0, "NHWC"),    # pointwise fwd over 128 channels, M = 243 (ragged)
-    (3, 136, 9, 9, 64, 1, 1, 1, 0, "NHWC"),     # pointwise dgrad: 64 -> 136 channels (one 8-wide chunk
+    (2, 64, 20, 20, 192, 1, 1, 1, 0, "NHWC"),   # 1x1 64 -> 192: second channel tile partial
+    (3, 128, 9, 9, 384, 1, 1, 1, 0, "NHWC"),    # 1x1 over 128 channels, M = 243 (ragged)
+    (3, 136, 9, 9, 64, 1, 1, 1, 0, "NHWC"),     # 1x1 dgrad 64 -> 136 channels (one 8-wide chunk
                                                 # in the second channel tile)
-    (5, 64, 56, 56, 256, 1, 1, 1, 0, "NHWC"),   # pointwise fwd / dgrad over many tiles per workgroup
-    (2, 256, 14, 14, 384, 1, 1, 1, 0, "NHWC"),  # pointwise fwd over 256 channels, 3 channel tiles
-    (2, 136, 9, 9, 256, 1, 1, 1, 0, "NHWC"),    # pointwise dgrad over 256: 136 outputs (ragged tile)
-    (3, 256, 40, 40, 1024, 1, 1, 1, 0, "NHWC"), # pointwise over 256, 38 tiles on 32 row groups
-    (5, 256, 28, 28, 200, 1, 1, 2, 0, "NHWC"),  # strided pointwise fwd over 256, ragged channels
-    # 3x3 stride 1 on the DMA-staged kernel at its edges:
+    (5, 64, 56, 56, 256, 1, 1, 1, 0, "NHWC"),   # 1x1 64 -> 256 over full-size images
+    (2, 256, 14, 14, 384, 1, 1, 1, 0, "NHWC"),  # 1x1 over 256 channels, 3 channel tiles
+    (2, 136, 9, 9, 256, 1, 1, 1, 0, "NHWC"),    # 1x1 dgrad over 256: 136 outputs (ragged tile)
+    (3, 256, 40, 40, 1024, 1, 1, 1, 0, "NHWC"), # 1x1 256 -> 1024, M = 4800
+    (5, 256, 28, 28, 200, 1, 1, 2, 0, "NHWC"),  # strided 1x1 over 256, ragged channels
+    # 3x3 stride 1 at its edges:
     (2, 64, 31, 31, 128, 3, 3, 1, 1, "NHWC"),   # odd row width, one 64-channel k-block per tap
     (3, 192, 5, 9, 136, 3, 3, 1, 1, "NHWC"),    # three k-blocks per tap, ragged second N tile
     (2, 128, 1, 13, 128, 3, 3, 1, 1, "NHWC"),   # one-row images: the outer tap rows all padding
@@ -204,12 +206,12 @@ def test_dgrad_add_parity(shape):
 # the data gradient from a filter rearranged ahead of time equals the one-call
 # data gradient bit for bit (with and without the addend)
 WF_SHAPES = [  # (n, c, h, w, k, r, stride, pad)
-    (2, 64, 28, 28, 64, 3, 1, 1),     # the 64-channel 3x3 kernel
-    (2, 128, 14, 14, 128, 3, 1, 1),   # DMA-staged kernel
+    (2, 64, 28, 28, 64, 3, 1, 1),     # 64-channel 3x3
+    (2, 128, 14, 14, 128, 3, 1, 1),
     (2, 64, 15, 15, 128, 1, 2, 0),    # strided 1x1: four phases, three of them empty
     (2, 32, 17, 17, 48, 3, 2, 1),     # strided 3x3: four phases of 1-4 taps
     (3, 16, 6, 5, 3, 3, 1, 2),        # 3 output channels, padded to 8 in the filter
-    (2, 64, 14, 14, 256, 1, 1, 0),    # pointwise kernel (64 -> 256 data gradient)
+    (2, 64, 14, 14, 256, 1, 1, 0),    # 1x1 (64 -> 256 data gradient)
 ]
 
 

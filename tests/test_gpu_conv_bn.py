@@ -19,13 +19,12 @@ pytestmark = pytest.mark.gpu
 
 EPS = 1e-5
 
-# n, c, h, k, r, stride, pad, post_scale, residual, relu, swap
+# n, c, h, k, r, stride, pad, post_scale, residual, relu, swap: mostly small
+# problems on the wide kernel; larger ones are in test_gpu_kernel_edges.py
 CASES = [
-    (2, 256, 56, 64, 1, 1, 0, 0.25, False, True, False),   # block conv1 + bn1 (register-direct kernel)
-    (4, 64, 56, 64, 3, 1, 1, 0.25, False, True, False),    # 3x3 64-channel: its own kernel, then
-                                                           # the BN's statistics pass
-    (2, 128, 28, 128, 3, 1, 1, 0.25, False, True, False),  # 3x3 128-channel: DMA-staged kernel
-                                                           # with the statistics epilogue
+    (2, 256, 56, 64, 1, 1, 0, 0.25, False, True, False),   # block conv1 + bn1
+    (4, 64, 56, 64, 3, 1, 1, 0.25, False, True, False),    # 3x3 64-channel
+    (2, 128, 28, 128, 3, 1, 1, 0.25, False, True, False),  # 3x3 128-channel
     (2, 64, 28, 256, 1, 1, 0, 0.25, True, True, False),    # block conv3 + bn3 with the shortcut
     (3, 64, 7, 128, 3, 1, 1, 0.25, False, True, False),    # M = 147: ragged last band
     (3, 64, 9, 64, 3, 1, 1, 0.25, False, True, False),     # M = 243, 64 channels: ragged band, narrow tile
@@ -35,21 +34,19 @@ CASES = [
     (2, 64, 14, 256, 1, 1, 0, 0.25, True, True, True),     # BN swap on the block-last BN
     (2, 128, 15, 64, 3, 2, 1, 0.25, False, False, False),  # strided, no ReLU
     (32, 256, 56, 64, 1, 1, 0, 0.25, False, True, False),  # the conv2_x block's conv1 at batch 32
-    (3, 128, 9, 384, 1, 1, 0, 0.25, False, True, False),   # pointwise kernel over 128 channels,
-                                                           # ragged rows and channel tiles
-    (5, 64, 56, 256, 1, 1, 0, 0.25, True, True, False),    # pointwise, many tiles per workgroup
+    (3, 128, 9, 384, 1, 1, 0, 0.25, False, True, False),   # 1x1 over 128 channels, ragged rows
+                                                           # and channel tiles
+    (5, 64, 56, 256, 1, 1, 0, 0.25, True, True, False),    # 1x1 64 -> 256 with the shortcut
     (6, 64, 212, 64, 1, 1, 0, 0.25, False, True, False),   # 2,107 tile records (ragged): the
                                                            # statistics take the sliced two-kernel path
     (21, 64, 56, 256, 1, 1, 0, 0.25, True, True, False),   # pointwise: 515 tiles over 512 workgroup
                                                            # records, the ragged last tile in record 2
-    (21, 128, 28, 512, 1, 1, 0, 0.25, True, True, False),  # pointwise over 128 channels: 129 tiles
-                                                           # over 128 records (tiles 0 and 128 in one)
-    (2, 64, 20, 192, 1, 1, 0, 0.25, True, False, False),  # pointwise over 64, its second pass
-                                                           # applying the BN: no ReLU, ragged tile
+    (21, 128, 28, 512, 1, 1, 0, 0.25, True, True, False),  # 1x1 128 -> 512 with the shortcut
+    (2, 64, 20, 192, 1, 1, 0, 0.25, True, False, False),  # 1x1 64 -> 192: no ReLU, ragged tile
     (3, 64, 9, 256, 1, 1, 0, 0.25, False, True, False),    # ... no shortcut, ragged rows
-    (3, 256, 40, 1024, 1, 1, 0, 0.25, True, True, False),  # pointwise over 256: 38 tiles on 32 records
-    (2, 256, 14, 136, 1, 1, 0, 0.25, False, True, False),  # pointwise over 256, ragged channel tile
-    (4, 256, 28, 512, 1, 2, 0, 0.25, False, True, False),  # strided pointwise over 256 (the conv3_x
+    (3, 256, 40, 1024, 1, 1, 0, 0.25, True, True, False),  # 1x1 256 -> 1024, M = 4800
+    (2, 256, 14, 136, 1, 1, 0, 0.25, False, True, False),  # 1x1 over 256, ragged channel tile
+    (4, 256, 28, 512, 1, 2, 0, 0.25, False, True, False),  # strided 1x1 over 256 (the conv3_x
                                                            # shortcut's shape)
 ]
 
@@ -116,12 +113,15 @@ def test_conv_bn_in_place_output():
     assert torch.equal(Y2.view(torch.int16), Z.view(torch.int16))
 
 
+POINTWISE_IN_PLACE = (32, 64, 28, 256)  # n, c, h, k: 392 tiles
+
+
 @pytest.mark.parametrize("alias", ["z_is_y", "z_is_residual"])
 def test_conv_bn_pointwise_in_place(alias):
     # the pointwise kernel over 64 channels applies the BN in a second pass
     # that recomputes y from x: z may still be y, or the shortcut it reads
     require_gpu()
-    n, c, h, k = 2, 64, 28, 256
+    n, c, h, k = POINTWISE_IN_PLACE
     cd = F.conv_desc(n, c, h, h, k, 1, 1, 1, 0)
     bd = F.bn_desc(n, k, h, h, "NHWC", EPS, 0.25, True)
     x = synth.normal_f16((n, h, h, c), 1.0, 71, 1)

@@ -1,7 +1,9 @@
 """GPU checks of fp16_conv_dgrad_wf_m: the data gradient plus an addend taken
 under a ReLU mask (the input gradient of a residual block, Section 4.1,
 where the identity shortcut's gradient is the block-last BN's incoming
-gradient through its ReLU), on every kernel the data gradient can take.
+gradient through its ReLU), on small problems and on layers of ResNet-50 (the
+kernels besides the wide one, at the sizes that take them, are in
+test_gpu_kernel_edges.py).
 
 Bars: bit-identical to fp16_conv_dgrad_wf on the addend with the masked-off
 elements replaced by +0 (built on the host from the mask bits), and within
@@ -20,17 +22,17 @@ pytestmark = pytest.mark.gpu
 
 # (n, c, h, w, k, r, stride, pad): dy has k channels, dx (and the addend) c
 CASES = [
-    (2, 256, 14, 14, 64, 1, 1, 0),    # pointwise kernel, 64 -> 256 channels
-    (3, 128, 9, 9, 64, 1, 1, 0),      # pointwise kernel, 128-channel tiles, ragged rows
-    (2, 512, 7, 7, 128, 1, 1, 0),     # pointwise kernel over 128 channels
-    (2, 256, 7, 7, 512, 1, 1, 0),     # DMA-staged kernel (512-long reduction)
-    (2, 64, 9, 9, 512, 1, 1, 0),      # DMA-staged kernel, 64-channel tiles
-    (2, 64, 10, 10, 256, 1, 1, 0),    # register-direct kernel
-    (2, 64, 14, 14, 64, 3, 2, 1),     # four stride phases, register-direct
-    (2, 128, 14, 14, 256, 3, 2, 1),   # four stride phases, DMA-staged
-    (2, 16, 9, 9, 24, 3, 1, 1),       # LDS-staged kernel (24 channels)
+    (2, 256, 14, 14, 64, 1, 1, 0),    # 1x1, 64 -> 256 channels
+    (3, 128, 9, 9, 64, 1, 1, 0),      # 1x1, ragged rows
+    (2, 512, 7, 7, 128, 1, 1, 0),     # 1x1 over 128 channels
+    (2, 256, 7, 7, 512, 1, 1, 0),     # 512-long reduction
+    (2, 64, 9, 9, 512, 1, 1, 0),      # ... 64 outputs
+    (2, 64, 10, 10, 256, 1, 1, 0),    # 256-long reduction, 64 outputs
+    (2, 64, 14, 14, 64, 3, 2, 1),     # four stride phases
+    (2, 128, 14, 14, 256, 3, 2, 1),   # ... over 256 channels
+    (2, 16, 9, 9, 24, 3, 1, 1),       # 24 channels
     (32, 256, 56, 56, 64, 1, 1, 0),   # the conv2_x block input gradient at batch 32
-    (2, 512, 14, 14, 256, 1, 1, 0),   # register-direct kernel, 256-long reduction
+    (2, 512, 14, 14, 256, 1, 1, 0),   # 256-long reduction
     (3, 1024, 40, 40, 256, 1, 1, 0),  # ... over many tiles
 ]
 
@@ -81,15 +83,15 @@ def test_masked_addend(case, in_place):
 # (n, c, h, w, k, r, stride, pad, addend stride, with mask): fp16_conv_dgrad_wf_ex
 # with the addend on every s-th row and column
 STRIDED = [
-    (2, 256, 14, 14, 128, 1, 1, 0, 2, False),   # pointwise kernel (the conv3_x block input)
-    (2, 256, 15, 13, 64, 1, 1, 0, 2, False),    # pointwise, odd sides (ceil grid)
-    (2, 512, 14, 14, 256, 1, 1, 0, 2, False),   # register-direct kernel (the conv4_x block input)
-    (2, 1024, 7, 7, 512, 1, 1, 0, 2, False),    # DMA-staged kernel (the conv5_x block input)
-    (2, 16, 9, 9, 24, 3, 1, 1, 3, False),       # LDS-staged kernel, stride 3
+    (2, 256, 14, 14, 128, 1, 1, 0, 2, False),   # the conv3_x block input
+    (2, 256, 15, 13, 64, 1, 1, 0, 2, False),    # odd sides (ceil grid)
+    (2, 512, 14, 14, 256, 1, 1, 0, 2, False),   # the conv4_x block input
+    (2, 1024, 7, 7, 512, 1, 1, 0, 2, False),    # the conv5_x block input
+    (2, 16, 9, 9, 24, 3, 1, 1, 3, False),       # addend stride 3
     (2, 64, 14, 14, 64, 3, 2, 1, 2, False),     # stride phases of the data gradient itself
     (2, 256, 14, 14, 128, 1, 1, 0, 2, True),    # with a mask over the strided addend
     (2, 512, 10, 10, 256, 1, 1, 0, 2, True),
-    (3, 1024, 40, 40, 256, 1, 1, 0, 2, False),  # register-direct kernel over many tiles
+    (3, 1024, 40, 40, 256, 1, 1, 0, 2, False),  # many tiles
     (32, 256, 56, 56, 128, 1, 1, 0, 2, False),  # the conv3_x block input gradient at batch 32
 ]
 

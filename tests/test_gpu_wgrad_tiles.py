@@ -14,21 +14,32 @@ from gpu_util import note, require_gpu
 
 pytestmark = pytest.mark.gpu
 
-# (n, c, h, w, k, r, stride)
-SHAPES = [
-    (3, 128, 11, 13, 128, 3, 1),   # 128 x 128
-    (2, 512, 7, 7, 512, 3, 1),     # 256 x 128 (144 tiles of 128 x 128)
-    (2, 688, 12, 12, 384, 3, 1),   # 128 x 256
-    (5, 72, 15, 17, 200, 3, 2),    # channels that are multiples of 8 only: ragged tiles, taps per lane
-    (2, 24, 20, 21, 72, 5, 1),     # several taps in a 64-column block, 72 of 128 output channels
-    (4, 64, 9, 9, 64, 3, 1),       # 64 x 192
-    (3, 200, 8, 8, 40, 3, 1),      # 64 x 256, 40 output channels
-    (2, 136, 10, 10, 64, 1, 1),    # 64 x 128
-    (2, 56, 10, 10, 32, 1, 1),     # 64 x 64
-    (3, 40, 9, 11, 136, 1, 1),     # 128 x 64
-    (1, 8, 1, 1, 80, 1, 1),        # one pixel
-    (1, 96, 3, 67, 96, 3, 1),      # rows longer than a k-step
+# (n, c, h, w, k, r, stride) and the tile ("taps": a filter tap per lane; checked
+# on the host in test_kernel_choice.py)
+TILES = [
+    ((3, 128, 11, 13, 128, 3, 1), "128x128 8 waves"),
+    ((2, 512, 7, 7, 512, 3, 1), "128x128 8 waves"),
+    ((8, 384, 14, 15, 136, 5, 1), "256x128 8 waves"),
+    ((32, 1000, 7, 8, 136, 3, 1), "256x128 8 waves taps"),  # ragged rows of 256, taps per lane
+    ((16, 256, 11, 12, 264, 5, 1), "128x256 8 waves"),  # ragged rows
+    ((32, 688, 7, 8, 72, 5, 1), "128x256 8 waves taps"),  # taps per lane
+    ((2, 688, 12, 12, 384, 3, 1), "128x128 8 waves taps"),
+    ((5, 72, 15, 17, 200, 3, 2), "128x128 8 waves taps"),  # channels that are multiples of 8 only: ragged tiles
+    ((2, 24, 20, 21, 72, 5, 1), "128x128 8 waves taps"),  # several taps in a 64-column block, 72 of 128 output channels
+    ((4, 64, 9, 9, 64, 3, 1), "64x192 4 waves"),
+    ((3, 200, 8, 8, 40, 3, 1), "64x192 4 waves taps"),  # 40 output channels
+    ((2, 136, 10, 10, 64, 1, 1), "64x192 4 waves taps"),
+    ((2, 120, 10, 10, 64, 1, 1), "64x128 4 waves taps"),
+    ((2, 56, 10, 10, 32, 1, 1), "64x64 4 waves taps"),
+    ((3, 40, 9, 11, 136, 1, 1), "128x64 4 waves taps"),
+    ((1, 8, 1, 1, 80, 1, 1), "128x64 4 waves taps"),  # one pixel
+    ((1, 688, 7, 8, 136, 5, 1), "128x64 4 waves taps"),  # many tiles of a few k-steps
+    ((1, 512, 5, 5, 1000, 3, 1), "128x64 4 waves"),  # ... with 64-channel blocks
+    ((1, 96, 3, 67, 96, 3, 1), "128x128 8 waves taps"),  # rows longer than a k-step
+    ((4, 64, 21, 21, 256, 3, 2), "128x128 8 waves"),
+    ((2, 48, 16, 16, 64, 5, 1), "64x256 8 waves taps"),
 ]
+SHAPES = [t[0] for t in TILES]
 
 
 @pytest.mark.parametrize("shape", SHAPES, ids=["x".join(map(str, s)) for s in SHAPES])

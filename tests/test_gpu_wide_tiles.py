@@ -1,7 +1,8 @@
 """The wide implicit-GEMM kernel at every tile shape its rule picks (64 to 256
 rows x 128 channels, 128 and 256 rows x 64), against float64 convolutions in
 plain torch: ragged rows and channels, channel counts that are multiples of
-64, of 8 or neither, strided phases, addends and masks, BN statistics.
+64, of 8 or neither, strided phases, addends and masks (every tile but 128 x 64
+and 64 x 128 in the form with a tap per lane and in the other), BN statistics.
 
 Bound per element: one rounding to binary16 (2^-11 of the value, 2^-25 below
 the normal range) plus the float32 sum's K * 2^-24 * sum |a b|."""
@@ -47,26 +48,39 @@ def check(got, ref, mag, K):
     note(f"largest error over its bound {over:.3f}")
 
 
-# (n, c, h, w, k, r, stride): output rows n*P*Q pick the tile (one workgroup
-# per CU: up to 16384 rows 64, 32768 128, 40960 160, 49152 192, 57344 224,
-# 65536 256 for one channel tile; up to 64 channels 128 x 64 and 256 x 64)
-SHAPES = [
-    (1, 64, 9, 7, 72, 3, 1),       # 64 rows, one partial tile
-    (2, 128, 90, 91, 100, 3, 1),   # 64 rows, channels not a multiple of 8
-    (1, 64, 130, 127, 128, 3, 1),  # 128 rows
-    (1, 72, 190, 185, 96, 3, 1),   # 160 rows, a tap per lane
-    (1, 64, 211, 213, 128, 3, 1),  # 192 rows
-    (1, 64, 237, 232, 72, 3, 1),   # 224 rows
-    (1, 24, 237, 231, 88, 3, 1),   # 224 rows, several taps per 128-byte row
-    (1, 64, 255, 256, 104, 3, 1),  # 256 rows
-    (1, 136, 254, 250, 128, 3, 1), # 256 rows, a tap per lane
-    (1, 64, 129, 131, 40, 5, 1),   # 128 x 64
-    (1, 40, 131, 131, 64, 3, 1),   # 128 x 64, a tap per lane
-    (1, 96, 201, 205, 64, 3, 1),   # 256 x 64
-    (2, 8, 33, 35, 64, 9, 2),      # 81 taps
-    (3, 192, 29, 31, 320, 3, 2),   # strided, three channel tiles
-    (1, 13, 20, 21, 21, 3, 1),     # odd channels (padded), scalar stores
+# (n, c, h, w, k, r, stride), then the tile of the forward, of the forward with
+# statistics and of the data gradient (with or without an addend); "taps": a
+# filter tap per lane.  (Checked on the host in test_kernel_choice.py.)
+TILES = [
+    ((1, 64, 9, 7, 72, 3, 1), "64x128", "64x128", "64x128 taps"),
+    ((2, 128, 90, 91, 100, 3, 1), "64x128", "64x128", "64x128 taps"),
+    ((1, 64, 130, 127, 128, 3, 1), "64x128", "128x128", "128x64"),
+    ((1, 72, 190, 185, 96, 3, 1), "160x128 taps", "160x128 taps", "160x128 taps"),
+    ((1, 64, 211, 213, 128, 3, 1), "192x128", "192x128", "256x64"),
+    ((1, 64, 237, 232, 72, 3, 1), "224x128", "224x128", "256x64 taps"),
+    ((1, 24, 237, 231, 88, 3, 1), "224x128 taps", "224x128 taps", "256x64 taps"),
+    ((1, 64, 255, 256, 104, 3, 1), "256x128", "256x128", "256x64 taps"),
+    ((1, 136, 254, 250, 128, 3, 1), "256x128 taps", "256x128 taps", "256x128"),
+    ((1, 64, 129, 131, 40, 5, 1), "128x64", "128x64", "128x64 taps"),
+    ((1, 40, 131, 131, 64, 3, 1), "128x64 taps", "128x64 taps", "128x64"),
+    ((1, 96, 201, 205, 64, 3, 1), "256x64 taps", "256x64 taps", "192x128"),
+    ((2, 8, 33, 35, 64, 9, 2), "64x128 taps", "64x128 taps", "64x128"),
+    ((3, 192, 29, 31, 320, 3, 2), "64x128", "64x128", "64x128"),
+    ((1, 13, 20, 21, 21, 3, 1), "64x128 taps", "64x128 taps", "64x128 taps"),
+    ((1, 128, 130, 131, 128, 3, 1), "128x128", "128x128", "128x128"),
+    ((1, 104, 130, 131, 72, 3, 1), "128x128 taps", "128x128 taps", "128x128 taps"),
+    ((1, 72, 181, 182, 64, 3, 1), "256x64 taps", "256x64 taps", "160x128"),
+    ((1, 104, 181, 182, 72, 3, 1), "160x128 taps", "160x128 taps", "160x128 taps"),
+    ((1, 72, 202, 203, 64, 3, 1), "256x64 taps", "256x64 taps", "192x128"),
+    ((1, 104, 202, 203, 72, 3, 1), "192x128 taps", "192x128 taps", "192x128 taps"),
+    ((1, 72, 223, 224, 64, 3, 1), "256x64 taps", "256x64 taps", "224x128"),
+    ((1, 104, 223, 224, 72, 3, 1), "224x128 taps", "224x128 taps", "224x128 taps"),
+    ((1, 72, 241, 242, 64, 3, 1), "256x64 taps", "256x64 taps", "256x128"),
+    ((1, 104, 241, 242, 72, 3, 1), "256x128 taps", "256x128 taps", "256x128 taps"),
+    ((1, 64, 180, 361, 64, 5, 1), "256x64", "256x64", "256x64"),
+    ((1, 128, 181, 182, 128, 3, 1), "160x128", "160x128", "160x128"),
 ]
+SHAPES = [t[0] for t in TILES]
 
 
 @pytest.mark.parametrize("shape", SHAPES, ids=["x".join(map(str, s)) for s in SHAPES])
@@ -130,8 +144,8 @@ def test_wide_statistics(shape):
     assert torch.equal(y0, y1)
     v = y1.double().view(-1, k)
     mean, var = v.mean(0), v.var(0, unbiased=False)
-    # float32 sums of at most 256 * 2^7 rows per record about one of its
-    # values: well inside 2e-6 of the spread
+    # float32 sums of at most 256 rows per record about one of its values:
+    # well inside 2e-6 of the spread
     sd = (var + 1e-5).sqrt()
     assert ((stats[:k].double() - mean).abs() / sd).max().item() < 2e-6
     assert ((stats[k:].double() * sd) - 1).abs().max().item() < 4e-6
