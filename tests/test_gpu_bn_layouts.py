@@ -98,3 +98,86 @@ def test_layouts(shape, form):
         elif res is not None:
             assert torch.equal(dres.view(M, c), torch.where(mask, dy.view(M, c), torch.zeros_like(x.view(M, c))))
     assert torch.equal(a[1], b[1])
+
+
+# tensors of over 190 MB, which with the others of a pass exceed the memory-side
+# cache: the reduces take rows in turn and the applies go from the end
+@pytest.mark.parametrize("form", ["plain", "residual", "stored", "swap", "mask"])
+@pytest.mark.parametrize("shape", [(1, 64, 1063, 1409), (3, 40, 911, 907)],
+                         ids=["64ch", "40ch"])  # a power of two of chunks, and 5
+def test_beyond_the_cache(shape, form):
+    """Forward and backward element by element against float64, sampled rows at
+    both ends and between; sums whole."""
+    require_gpu()
+    n, c, h, w = shape
+    M, swap, masked = n * h * w, form == "swap", form == "mask"
+    g = torch.Generator(device="cuda")
+    g.manual_seed(33)
+
+    def rnd(*s, std=1.0, mean=0.0):
+        return (torch.randn(s, generator=g, device="cuda") * std + mean).half()
+
+    x, dy = rnd(n, h, w, c, mean=0.2), rnd(n, h, w, c, std=1e-2)
+    gamma, beta = rnd(c, std=0.3, mean=1.0), rnd(c, std=0.3)
+    res = None if form == "plain" else rnd(n, h, w, c)
+    d = F.bn_desc(n, c, h, w, "NHWC", EPS, SCALE, True, swap=swap)
+    if masked and not F.fp16_bn_mask_bytes(d):
+        pytest.skip("no kept mask at this channel count")
+    ws = F.workspace(F.fp16_bn_workspace_bytes(d))
+    st = torch.empty(2 * c, dtype=torch.float32, device="cuda")
+    y = torch.full_like(x, float("nan"))
+    if masked:
+        m = torch.zeros(F.fp16_bn_mask_bytes(d), dtype=torch.uint8, device="cuda")
+        F.fp16_bn_relu_m(d, x, gamma, beta, res, y, st, m, ws)
+    else:
+        F.fp16_bn_relu(d, x, gamma, beta, res, y, st, ws)
+    x2 = x.view(M, c)
+    mean = x2.double().mean(0)
+    var = (x2.double() - mean).square_().mean(0)
+    sd = (var + EPS).sqrt()
+    assert ((st[:c].double() - mean).abs() / sd).max().item() < 2e-6
+    assert ((st[c:].double() * sd) - 1).abs().max().item() < 4e-6
+    dx, dres = torch.full_like(x, float("nan")), torch.full_like(x, float("nan"))
+    dg, db = torch.empty_like(gamma), torch.empty_like(beta)
+    if masked:
+        F.fp16_bn_relu_bwd_m(d, x, m, dy, gamma, beta, st, dx, dg, db, dres, ws)
+    else:
+        F.fp16_bn_relu_bwd(d, x, y if form == "stored" else None, dy, gamma, beta, res, st, dx, dg,
+                           db, None if res is None else dres, ws)
+    keep = y.view(M, c) > 0
+    A, rs = gamma.double(), st[c:].double()
+    s1, s2, s3, mag = (torch.zeros(c, dtype=torch.float64, device="cuda") for _ in range(4))
+    step = 1 << 18
+    for i in range(0, M, step):
+        b = slice(i, i + step)
+        G = SCALE * dy.view(M, c)[b].double() * keep[b]
+        xh = (x2[b].double() - st[:c].double()) * rs
+        s1 += G.sum(0)
+        s2 += (G * xh).sum(0)
+        mag += (G.abs() * (1 + xh.abs())).sum(0)
+        if swap:
+            s3 += (G * res.view(M, c)[b].double()).sum(0)
+            mag += (G * res.view(M, c)[b].double()).abs().sum(0)
+    # (float32 sums at most 256 additions deep, then float64)
+    tol = 2.0 ** -16 * mag + 2.0 ** -25
+    assert ((db.double() - s1).abs() <= s1.abs() * 2.0 ** -11 + tol).all()
+    assert ((dg.double() - (s2 + s3)).abs() <= (s2 + s3).abs() * 2.0 ** -11 + tol).all()
+    for i in range(0, M, step):
+        b = slice(i, i + step)
+        G = SCALE * dy.view(M, c)[b].double() * keep[b]
+        xh = (x2[b].double() - st[:c].double()) * rs
+        ref = A * rs * (G - s1 / M - xh * (s2 / M))
+        parts = (A * rs).abs() * (G.abs() + (s1 / M).abs() + (xh * (s2 / M)).abs() + mag / M)
+        err = (dx.view(M, c)[b].double() - ref).abs()
+        assert (err <= ref.abs() * 2.0 ** -11 + 1e-5 * parts + 2.0 ** -25).all()
+        r = 0.0 if res is None else res.view(M, c)[b].double()
+        v = SCALE * (A * (xh + r) + beta.double()) if swap else SCALE * (A * xh + beta.double()) + r
+        fw = (y.view(M, c)[b].double() - v.clamp_min(0)).abs()
+        assert (fw <= v.abs() * 2.0 ** -11 + 2e-6 * (A * xh).abs() + 1e-5).all()
+        if res is not None:
+            got = dres.view(M, c)[b]
+            if swap:
+                want = A * G
+                assert ((got.double() - want).abs() <= want.abs() * 2.0 ** -10 + 2.0 ** -24).all()
+            else:
+                assert torch.equal(got, torch.where(keep[b], dy.view(M, c)[b], torch.zeros_like(got)))
