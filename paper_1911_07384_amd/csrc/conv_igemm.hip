@@ -2309,7 +2309,8 @@ Shape shape_of(const IgemmArgs& a) {
 // layers tried: batch 128, 14x14 256 -> 256 3x3 224 rows 32.4 us against 33.7
 // at 256 and 42.7 at 128; 28x28 128 -> 128 224 rows 39.5 against 42; 7x7 512 ->
 // 512 128 rows 36.5 against 40.2 at 160; batch 32, 7x7 2048 -> 512 64 rows 12.7
-// against 16.4 at 128.)  Of the two smallest shapes (64 x 128 and 128 x 64, 72
+// against 16.4 at 128, 28x28 320 -> 320 1x1 160 rows 14.2 against 15.4 and more;
+// batch 128, 45x45 16 -> 200 3x3/2 192 rows 20.6 against 21.3 and more.)  Of the two smallest shapes (64 x 128 and 128 x 64, 72
 // KB of LDS) two workgroups share a CU: a pair takes about as long as one tile
 // of twice the size, less where the reduction is short and one's stores run
 // under the other's loads (batch 128, 56x56 64 -> 64 3x3 with an addend 66.3 us
