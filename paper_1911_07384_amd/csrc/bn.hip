@@ -182,7 +182,7 @@ __device__ __forceinline__ void block_reduce_vec(float (&sums)[NS][8], float* re
 // (a shift that keeps the variance free of cancellation).
 
 __global__ __launch_bounds__(kT) void bn_fwd_reduce_vec(const h16* __restrict__ x, Geo g, int CV,
-                                                        int RB, int64_t nsteps, int far, float* ws) {
+                                                        int RB, int64_t nsteps, float* ws) {
   __shared__ float red[16 * kT];
   const int t = threadIdx.x;
   const int j = t % CV;
@@ -195,25 +195,22 @@ __global__ __launch_bounds__(kT) void bn_fwd_reduce_vec(const h16* __restrict__ 
     sums[1][e] = 0.0f;
   }
   // four rows in flight per thread, the sums row by row; the step count is
-  // the launch's, and a row past the block's last is loaded clamped (in
-  // bounds) and adds exact zeros, so no load waits behind a condition
+  // the launch's, and a row past the last is loaded clamped (in bounds) and
+  // adds exact zeros, so no load waits behind a condition
   const bool act = t < RB * CV;
-  // (far: the workgroups take rows in turn, through the tensor together)
-  const int64_t row0 = (int64_t)blockIdx.x * RB * (far ? 1 : nsteps);
-  const int64_t RS = (int64_t)RB * (far ? gridDim.x : 1);
-  const int64_t row1 = !far && row0 + nsteps * RB < g.M ? row0 + nsteps * RB : g.M;
-  const int64_t rt = row0 + t / CV;
+  const int64_t rt = (int64_t)blockIdx.x * RB + t / CV;
+  const int64_t RS = (int64_t)RB * gridDim.x;
   for (int64_t i = 0; i < nsteps; i += 4) {
     V8 v[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int64_t row = rt + (i + u) * RS;
-      v[u] = load16(x + (row < row1 ? row : row1 - 1) * g.C + j * 8);
+      v[u] = load16(x + (row < g.M ? row : g.M - 1) * g.C + j * 8);
     }
     __builtin_amdgcn_sched_barrier(0);  // every load issued before the first use
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const bool ok = act && rt + (i + u) * RS < row1;
+      const bool ok = act && rt + (i + u) * RS < g.M;
 #pragma unroll
       for (int e = 0; e < 8; ++e) {
         const float d = ok ? to_f32(v[u].h[e]) - sh[e] : 0.0f;
@@ -549,7 +546,8 @@ __global__ __launch_bounds__(64) void bn_band_combine(const float* __restrict__ 
 //   the stored output y; kLoadR: the shortcut r is read; kDres: the backward
 //   writes the shortcut gradient; kMaskB: the backward takes the ReLU mask
 //   from the bits the forward kept; kKeepF: the forward apply keeps them (one
-//   byte per 16-byte vector of y, bit e = [y element e > 0]); kFar: see beyond_cache.
+//   byte per 16-byte vector of y, bit e = [y element e > 0]); kFar: the
+//   forward apply loads x past the caches.
 constexpr int kSwap = 1, kRelu = 2, kMaskY = 4, kLoadR = 8, kDres = 16, kMaskB = 32, kKeepF = 64,
               kFar = 128;
 
@@ -563,19 +561,25 @@ constexpr int kSwap = 1, kRelu = 2, kMaskY = 4, kLoadR = 8, kDres = 16, kMaskB =
 // discarded).
 constexpr int kApplyU = 4;
 
-template <bool FAR>
-__device__ __forceinline__ V8 load_once(const h16* p) {
-  if (!FAR) return load16(p);
+// The applies walk the tensor backwards (run r from the end): the pass before
+// them -- the reduce, whose workgroups advance through it together, or the
+// convolution that wrote x -- left the memory-side cache (256 MB) holding the
+// tensor's end.  x and dy in the backward, and x in the forward after a
+// convolution that gave the statistics, are loaded past that cache and the
+// shortcut gradient stored past it, so that they do not push out what the
+// following calls read.  Forward and backward in turn over new inputs: [128, 56,
+// 56, 256] after its 1x1 convolution 462 us (ordinary walk and loads 485), the
+// ResNet-50 step 11.04 ms (11.30).  A forward that has read x for its own
+// statistics loads it again through the cache: [32, 56, 56, 256] 89.1 us against
+// 103.9 past it, [128, 28, 28, 512] 155 against 181, [128, 56, 56, 256] 300
+// against 318.
+__device__ __forceinline__ V8 load_far(const h16* p) {
   V8 v;
   v.u = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
   return v;
 }
-template <bool FAR>
-__device__ __forceinline__ void store_once(h16* p, const V8& v) {
-  if (FAR)
-    __builtin_nontemporal_store(v.u, reinterpret_cast<u32x4*>(p));
-  else
-    store16(p, v);
+__device__ __forceinline__ void store_far(h16* p, const V8& v) {
+  __builtin_nontemporal_store(v.u, reinterpret_cast<u32x4*>(p));
 }
 
 template <int MODE>
@@ -594,14 +598,14 @@ __global__ __launch_bounds__(kT) void bn_fwd_apply_vec(const h16* x, const h16* 
   const int64_t nvec = g.M * CV;
   const int64_t RUN = (int64_t)kApplyU * TV;
   const int64_t nruns = (nvec + RUN - 1) / RUN;
-  for (int64_t r = blockIdx.x; r < nruns; r += gridDim.x) {
-    const int64_t run = (FAR ? nruns - 1 - r : r) * RUN;
+  for (int64_t r = nruns - 1 - blockIdx.x; r >= 0; r -= gridDim.x) {
+    const int64_t run = r * RUN;
     V8 xv[kApplyU], rv[kApplyU];
 #pragma unroll
     for (int u = 0; u < kApplyU; ++u) {
       const int64_t v = run + t + u * TV;
       const int64_t vc = v < nvec ? v : nvec - 1;
-      xv[u] = load_once<FAR>(x + vc * 8);
+      xv[u] = FAR ? load_far(x + vc * 8) : load16(x + vc * 8);
       if (HAS_R) rv[u] = load16(res + vc * 8);
     }
     __builtin_amdgcn_sched_barrier(0);  // every load issued before the first use
@@ -649,8 +653,8 @@ __global__ __launch_bounds__(kT) void bn_bwd_reduce_vec(const h16* __restrict__ 
                                                         const h16* __restrict__ beta,
                                                         const h16* __restrict__ res,
                                                         const float* __restrict__ stats, Geo g,
-                                                        int CV, int RB, int64_t nsteps, int far,
-                                                        float s, float* ws, uint8_t* __restrict__ mbits) {
+                                                        int CV, int RB, int64_t nsteps, float s,
+                                                        float* ws, uint8_t* __restrict__ mbits) {
   constexpr bool SWAP = MODE & kSwap, RELU = MODE & kRelu, MASK_Y = MODE & kMaskY,
                  LOAD_R = MODE & kLoadR, MASK_B = MODE & kMaskB;
   // a mask recomputed from the shortcut is kept, one bit per element and one
@@ -678,14 +682,11 @@ __global__ __launch_bounds__(kT) void bn_bwd_reduce_vec(const h16* __restrict__ 
     uint32_t mb;
   };
   const bool act = t < RB * CV;
-  // (far: the workgroups take rows in turn, through the tensor together)
-  const int64_t row0 = (int64_t)blockIdx.x * RB * (far ? 1 : nsteps);
-  const int64_t RS = (int64_t)RB * (far ? gridDim.x : 1);
-  const int64_t row1 = !far && row0 + nsteps * RB < g.M ? row0 + nsteps * RB : g.M;
-  const int64_t rt = row0 + t / CV;
+  const int64_t rt = (int64_t)blockIdx.x * RB + t / CV;
+  const int64_t RS = (int64_t)RB * gridDim.x;
   auto load_row = [&](Row& b, int64_t i) {
     int64_t row = rt + i * RS;
-    if (row >= row1) row = row1 - 1;
+    if (row >= g.M) row = g.M - 1;
     const int64_t off = row * g.C + j * 8;
     b.x = load16(x + off);
     b.d = load16(dy + off);
@@ -694,7 +695,7 @@ __global__ __launch_bounds__(kT) void bn_bwd_reduce_vec(const h16* __restrict__ 
     if (MASK_B) b.mb = mbits[row * CV + j];
   };
   auto sum_row = [&](const Row& b, int64_t i) {
-    const bool ok = act && rt + i * RS < row1;
+    const bool ok = act && rt + i * RS < g.M;
     uint32_t bits = 0;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
@@ -820,7 +821,7 @@ __global__ __launch_bounds__(kT) void bn_bwd_apply_vec(const h16* x, const h16* 
                                                        const uint8_t* __restrict__ mbits, h16* dx,
                                                        h16* dres) {
   constexpr bool SWAP = MODE & kSwap, RELU = MODE & kRelu, MASK_Y = MODE & kMaskY,
-                 DRES = MODE & kDres, FAR = MODE & kFar;
+                 DRES = MODE & kDres;
   // the ReLU mask recomputed from x and the shortcut was kept by the reduce,
   // or by the forward (kMaskB): one byte per vector instead of the
   // shortcut's 16
@@ -842,16 +843,16 @@ __global__ __launch_bounds__(kT) void bn_bwd_apply_vec(const h16* x, const h16* 
   constexpr int U = kApplyU / 2;  // vectors per thread and run: 2 to 4 loads each
   const int64_t RUN = (int64_t)U * TV;
   const int64_t nruns = (nvec + RUN - 1) / RUN;
-  for (int64_t r = blockIdx.x; r < nruns; r += gridDim.x) {
-    const int64_t run = (FAR ? nruns - 1 - r : r) * RUN;
+  for (int64_t r = nruns - 1 - blockIdx.x; r >= 0; r -= gridDim.x) {
+    const int64_t run = r * RUN;
     V8 xv[U], dv[U], yv[U];
     uint32_t mb[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int64_t v = run + t + u * TV;
       const int64_t vc = v < nvec ? v : nvec - 1;
-      xv[u] = load_once<FAR>(x + vc * 8);
-      dv[u] = load_once<FAR>(dy + vc * 8);
+      xv[u] = load_far(x + vc * 8);
+      dv[u] = load_far(dy + vc * 8);
       if (MASK_Y) yv[u] = load16(y + vc * 8);
       if (NEED_R) mb[u] = mbits[vc];
     }
@@ -875,7 +876,7 @@ __global__ __launch_bounds__(kT) void bn_bwd_apply_vec(const h16* x, const h16* 
       }
       if (t < TV && v < nvec) {
         store16(dx + v * 8, o);
-        if (DRES) store_once<FAR>(dres + v * 8, od);
+        if (DRES) store_far(dres + v * 8, od);
       }
     }
   }
@@ -1201,22 +1202,6 @@ unsigned apply_grid(int64_t nthreads_wanted) {
   return (unsigned)b;
 }
 
-// Whether a pass over `tensors` tensors of x's size, read and written, is more
-// than `times` the memory-side cache (256 MB).  There (kFar) the reduce's
-// workgroups take rows in turn, so that it, like the convolution that wrote x,
-// leaves the cache holding the tensor's end; the apply walks from the end and
-// loads what is read for the last time in a long while (x in the forward; x and
-// dy in the backward), and stores the shortcut gradient, past the cache, so that
-// they do not push out what the following calls read.  Forward and backward,
-// new inputs in each pass, the ordinary order second: [128, 56, 56, 256] backward
-// with a kept mask within its layer 462 us against 485, with a shortcut (forward
-// as well) 407 against 420; the ResNet-50 step 11,041 against 11,303.  Where the
-// tensors fit, the ordinary order is the faster: [32, 56, 56, 256] 104 against
-// 90, [128, 28, 28, 512] 181 against 158, [128, 14, 14, 256] 40.6 against 38.5.
-bool beyond_cache(const BnArgs& a, int tensors, int times = 1) {
-  return (int64_t)a.N * a.C * a.H * a.W * 2 * tensors > times * ((int64_t)256 << 20);
-}
-
 // Template variant of the vectorised kernels for these arguments.
 int fwd_mode(const BnArgs& a, const h16* res, bool keep) {
   return (a.swap ? kSwap : 0) | (a.relu ? kRelu : 0) | (res ? kLoadR : 0) | (keep ? kKeepF : 0);
@@ -1304,14 +1289,14 @@ static int nchw_chunks(const BnArgs& a) { return (a.H * a.W + 7) / 8; }
 
 // The batch statistics of x into stats (the partial sums in ws).
 static void bn_fwd_stats(const BnArgs& a, const Plan& p, const Geo& g, const h16* x, float* stats,
-                         void* ws, hipStream_t st, bool far = false) {
+                         void* ws, hipStream_t st) {
   float* part = reinterpret_cast<float*>(ws);
   if (p.nchw)
     hipLaunchKernelGGL(bn_fwd_reduce_nchw, dim3(p.G, a.C), dim3(kT), 0, st, x, g, nchw_chunks(a),
                        a.N * nchw_chunks(a), (int)p.rpb, part);
   else if (p.vec)
     hipLaunchKernelGGL(bn_fwd_reduce_vec, dim3(p.G), dim3(kT), 0, st, x, g, p.CV, p.RB, p.steps,
-                       far, part);
+                       part);
   else
     hipLaunchKernelGGL(bn_fwd_reduce_gen, dim3(p.G, a.C), dim3(kT), 0, st, x, g, p.rpb, part);
   if (p.vec && a.C >= kBmC)
@@ -1326,10 +1311,7 @@ hipError_t launch_bn_fwd(const BnArgs& a, const h16* x, const h16* gamma, const 
                          uint8_t* mout, hipStream_t st) {
   const Plan p = make_plan(a);
   const Geo g = make_geo(a);
-  // (without a shortcut the ordinary order is the faster at any size:
-  // [128, 56, 56, 256] 104 us against 118 on its own)
-  const bool far = res && beyond_cache(a, 3, 2);
-  if (!use_stats) bn_fwd_stats(a, p, g, x, stats, ws, st, far);
+  if (!use_stats) bn_fwd_stats(a, p, g, x, stats, ws, st);
   if (p.nchw) {
     const int PC = nchw_chunks(a), items = a.N * a.C * PC;
     const dim3 grid(apply_grid(items));
@@ -1342,7 +1324,7 @@ hipError_t launch_bn_fwd(const BnArgs& a, const h16* x, const h16* gamma, const 
   } else if (p.vec) {
     const hipError_t e =
         launch_fwd_apply_vec(fwd_mode(a, res, mout != nullptr), p, g, x, gamma, beta, res, y, stats,
-                             a.post_scale, far, mout, st);
+                             a.post_scale, false, mout, st);
     if (e != hipSuccess) return e;
   } else {
     hipLaunchKernelGGL(bn_fwd_apply_gen, dim3(apply_grid(g.M * a.C / 4)), dim3(kT), 0, st, x,
@@ -1361,7 +1343,7 @@ hipError_t launch_bn_fwd_maxpool(const BnArgs& a, const PoolArgs& pa, const h16*
                                  void* ws, h16* y, uint8_t* idx, hipStream_t st) {
   const Plan p = make_plan(a);
   const Geo g = make_geo(a);
-  if (!use_stats) bn_fwd_stats(a, p, g, x, stats, ws, st, beyond_cache(a, 2));
+  if (!use_stats) bn_fwd_stats(a, p, g, x, stats, ws, st);
   const int64_t total = (int64_t)pa.N * pa.P * pa.Q * (pa.C / 8);
   hipLaunchKernelGGL((bn_apply_maxpool_vec<3, 3>), dim3(apply_grid(total)), dim3(kT), 0, st,
                      x, gamma, beta, stats, a.post_scale, pa, y, idx);
@@ -1400,7 +1382,7 @@ hipError_t launch_bn_fwd_bands(const BnArgs& a, const float* part, int nb, int r
   if (p.vec) {
     const hipError_t e =
         launch_fwd_apply_vec(fwd_mode(a, res, mout != nullptr), p, g, x, gamma, beta, res, y, stats,
-                             a.post_scale, beyond_cache(a, res ? 3 : 2), mout, st);
+                             a.post_scale, true, mout, st);
     if (e != hipSuccess) return e;
   } else {
     hipLaunchKernelGGL(bn_fwd_apply_gen, dim3(apply_grid(g.M * a.C / 4)), dim3(kT), 0, st, x,
@@ -1423,7 +1405,6 @@ hipError_t launch_bn_bwd(const BnArgs& a, const h16* x, const h16* y, const h16*
                         : reinterpret_cast<uint8_t*>(ws) + partial_bytes(p, a.C) + coef_bytes(a.C);
   if (mask && (!p.whole || a.swap || !a.relu)) return hipErrorInvalidValue;
   const int mode = bwd_mode(a, y, res, dres, mask != nullptr);
-  const bool far = beyond_cache(a, dres ? 4 : 3);
   // NCHW: which of the stored output and the shortcut are read
   const bool hy = a.relu && y, lr = a.swap || (a.relu && !y && res);
   const int PC = nchw_chunks(a);
@@ -1450,7 +1431,7 @@ hipError_t launch_bn_bwd(const BnArgs& a, const h16* x, const h16* y, const h16*
 #define FP16K_CASE(m)                                                                          \
   case m:                                                                                      \
     hipLaunchKernelGGL(bn_bwd_reduce_vec<m>, dim3(p.G), dim3(kT), 0, st, x, y, dy, gamma, beta, \
-                       res, stats, g, p.CV, p.RB, p.steps, far, a.post_scale, part, mbits);      \
+                       res, stats, g, p.CV, p.RB, p.steps, a.post_scale, part, mbits);           \
     break;
       FP16K_BN_BWD_MODES(FP16K_CASE)
 #undef FP16K_CASE
@@ -1480,13 +1461,8 @@ hipError_t launch_bn_bwd(const BnArgs& a, const h16* x, const h16* y, const h16*
     switch (mode) {
 #define FP16K_CASE(m)                                                                          \
   case m:                                                                                      \
-    if (far)                                                                                   \
-      hipLaunchKernelGGL(bn_bwd_apply_vec<m | kFar>, grid, dim3(kT), 0, st, x, y, dy, gamma,   \
-                         beta, res, stats, coef, g, p.CV, p.TV, a.post_scale, mbits, dx,       \
-                         dres);                                                                \
-    else                                                                                       \
-      hipLaunchKernelGGL(bn_bwd_apply_vec<m>, grid, dim3(kT), 0, st, x, y, dy, gamma, beta,    \
-                         res, stats, coef, g, p.CV, p.TV, a.post_scale, mbits, dx, dres);      \
+    hipLaunchKernelGGL(bn_bwd_apply_vec<m>, grid, dim3(kT), 0, st, x, y, dy, gamma, beta, res, \
+                       stats, coef, g, p.CV, p.TV, a.post_scale, mbits, dx, dres);              \
     break;
       FP16K_BN_BWD_APPLY_MODES(FP16K_CASE)
 #undef FP16K_CASE

@@ -101,7 +101,7 @@ def test_layouts(shape, form):
 
 
 # tensors of over 190 MB, which with the others of a pass exceed the memory-side
-# cache: the reduces take rows in turn and the applies go from the end
+# cache: many runs per workgroup, taken from the end
 @pytest.mark.parametrize("form", ["plain", "residual", "stored", "swap", "mask"])
 @pytest.mark.parametrize("shape", [(1, 64, 1063, 1409), (3, 40, 911, 907)],
                          ids=["64ch", "40ch"])  # a power of two of chunks, and 5
